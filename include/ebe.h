@@ -77,7 +77,9 @@ typedef int32_t ebe_dtype;
  * speed): GATHER reads each element's nodal values straight from x; STAGED
  * copies a patch's node rows into LDS first, a few cases at a time;
  * PIPELINED is GATHER in persistent workgroups that fetch the next patch's
- * metadata while computing the current one; ASSEMBLED (linear level only)
+ * metadata while computing the current one (on the quadratic level with the
+ * patch's tetrahedra taken in fans around common edges, so nodes that
+ * neighbouring tetrahedra share are read and added once); ASSEMBLED (linear level only)
  * applies K1 assembled once (per material) into 3x3 blocks over the corner
  * graph instead of forming element products, so a product reads each block
  * once for all cases: a departure from the paper's element-by-element
@@ -398,8 +400,7 @@ ebe_status ebe_invert_lcurve(int32_t n_obs, int32_t n_basis, const double* G_dev
 /* ---- product forms and the autotuner ------------------------------------ */
 
 /* Time every product form of y = K x (level 0: quadratic mesh, level 1:
- * linear mesh) for (dtype, nrhs) on this mesh, and for GATHER, STAGED,
- * PIPELINED, COLOURED, DETERMINISTIC and ASSEMBLED every kernel variant
+ * linear mesh) for (dtype, nrhs) on this mesh, and for each form every kernel variant
  * (ebe_set_product_variant), and keep the
  * fastest for every later product with these
  * parameters (Section 4 tunes its kernels' parameters by hand; here the
@@ -420,10 +421,11 @@ ebe_status ebe_set_product_form(ebe_mesh* mesh, int32_t level, ebe_dtype dtype, 
 ebe_status ebe_get_product_form(const ebe_mesh* mesh, int32_t level, ebe_dtype dtype, int32_t nrhs,
                                 int32_t* form);
 
-/* Kernel variant of a form for (level, dtype, nrhs).  PIPELINED and
- * COLOURED: 0 = element geometry prefetched with the patch metadata and kept
+/* Kernel variant of a form for (level, dtype, nrhs).  PIPELINED on level 1:
+ * 0 = element geometry prefetched with the patch metadata and kept
  * in LDS (the default), 1 = read from the geometry cache by each work-item
- * of the element phase.  GATHER and STAGED: 0 = element geometry read from
+ * of the element phase; on level 0 PIPELINED and COLOURED have one kernel
+ * each and take every variant as 0.  GATHER and STAGED: 0 = element geometry read from
  * the mesh's geometry cache (the default), 1 = formed at every product from
  * the four corner coordinates (fewer bytes where few cases share an
  * element).  DETERMINISTIC: 0 = shared nodes' partial sums staged and

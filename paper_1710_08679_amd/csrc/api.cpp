@@ -56,6 +56,16 @@ ebe_status ensure_geometry(ebe_mesh* m, ebe_dtype dt, hipStream_t s) {
   return EBE_OK;
 }
 
+ebe_status ensure_fan_geometry(ebe_mesh* m, ebe_dtype dt, hipStream_t s) {
+  const int k = dt == EBE_F64 ? 0 : 1;
+  if (m->gfan_ready[k] || m->nfan == 0) return EBE_OK;
+  ebe_status st = m->gfan[k].alloc(size_t(m->nfan) * kFanLen * 16 * (dt == EBE_F64 ? 8 : 4));
+  if (st != EBE_OK) return st;
+  EBE_TRY_HIP(launch_fan_geometry(m, dt, m->gfan[k].as<void>(), s));
+  m->gfan_ready[k] = true;
+  return EBE_OK;
+}
+
 ebe_status ensure_assembled(ebe_mesh* m, ebe_dtype dt, hipStream_t s) {
   const int k = dt == EBE_F64 ? 0 : 1;
   if (m->k1.ready[k]) return EBE_OK;
@@ -131,9 +141,12 @@ ebe_status ensure_half(ebe_mesh* m, int level, hipStream_t s) {
 
 ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s) {
   ebe_status st = ensure_stage(m, nrhs, dt == EBE_F64 ? 8 : 4);
-  if (st == EBE_OK) st = ensure_geometry(m, dt, s);
-  if (st == EBE_OK && level == 1 && product_form(m, 1, dt, nrhs) == EBE_FORM_ASSEMBLED)
-    st = ensure_assembled(m, dt, s);
+  const int form = product_form(m, level == 0 ? 2 : 1, dt, nrhs);
+  if (st == EBE_OK && level == 0 && (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED))
+    st = ensure_fan_geometry(m, dt, s);
+  else if (st == EBE_OK)
+    st = ensure_geometry(m, dt, s);
+  if (st == EBE_OK && level == 1 && form == EBE_FORM_ASSEMBLED) st = ensure_assembled(m, dt, s);
   return st;
 }
 

@@ -34,6 +34,7 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
   const int order = level == 0 ? 2 : 1;
   ebe_status st = ensure_stage(m, nrhs, dt == EBE_F64 ? 8 : 4);
   if (st == EBE_OK) st = ensure_geometry(m, dt, s);
+  if (st == EBE_OK && level == 0) st = ensure_fan_geometry(m, dt, s);
   if (st == EBE_OK && level == 1) st = ensure_assembled(m, dt, s);
   if (st != EBE_OK) return st;
   hipEvent_t a = nullptr, b = nullptr;
@@ -45,14 +46,14 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
   for (int f = 0; f < EBE_NUM_FORMS; ++f) best[f] = DBL_MAX;
   for (int form = 0; form < EBE_NUM_FORMS && e == hipSuccess; ++form) {
     if (!form_usable(m, order, form, dt, nrhs)) continue;
-    // the patch kernels come in two variants: pipelined and coloured with
+    // the patch kernels come in two variants: pipelined (linear level) with
     // the element geometry kept in LDS or read per work-item, gather and
     // staged with the geometry read from the cache or formed from the corner
     // coordinates, deterministic with staging or colour by colour; the
     // assembled form comes in three tiles: measure them all
     const bool curved = order == 2 && m->curved;
     const int nvar = form == EBE_FORM_ASSEMBLED ? 3  // tiles: cases per work-item, slots per trip
-                     : (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED ||
+                     : ((form == EBE_FORM_PIPELINED && level == 1) ||
                         ((form == EBE_FORM_GATHER || form == EBE_FORM_STAGED) && !curved) ||
                         (form == EBE_FORM_DETERMINISTIC && m->pl[0].coff.size() > 1))
                          ? 2

@@ -120,6 +120,15 @@ struct Workspace {
 #ifndef EBE_PATCH_THREADS_F64
 #define EBE_PATCH_THREADS_F64 256
 #endif
+// Fans of the quadratic patches (pipelined and coloured forms, fan_kernel.h):
+// chains of at most kFanLen tetrahedra around a common edge.  A fan has
+// kFanWords node words (node id | patch-local id << kPtabLocalShift): the
+// spine's ends and mid node, then the spokes and rims; then two flag words
+// (tetrahedra in bits 0-1, the nodes' fix bits, three per node, ten nodes from
+// bit 2 of the first word, eight in the second).
+constexpr int kFanLen = 3;
+constexpr int kFanWords = 6 + 4 * kFanLen;
+constexpr int kFanStride = kFanWords + 2;
 constexpr int kSliceRows = 64;  // rows per slice of an assembled operator (AsmOp)
 constexpr int kA2MaxRow = 800;  // longest level-2 row (blocks) whose sums fit 64 KB of LDS
 constexpr int kPatchElems = EBE_PATCH_ELEMS;
@@ -149,8 +158,8 @@ struct PatchLevel {
   DBuf stage;   // staging buffer [nslots][3][nrhs] of the product's dtype
   int64_t nslots = 0, nshared = 0, entries = 0;
   int max_nodes = 0;
-  // element node words [E][10] (quadratic) or [E][4] (linear): node id |
-  // patch-local id << kPtabLocalShift; empty on meshes of 2^25 nodes or more
+  // element node words [E][4] (linear level): node id | patch-local id <<
+  // kPtabLocalShift; empty on meshes of 2^25 nodes or more
   DBuf ptab;
   // colouring of the patches (quadratic level): no two patches of a colour
   // share a node; cperm lists the patches colour by colour (increasing id
@@ -196,12 +205,16 @@ struct ebe_mesh {
   ebe::DBuf lconn;      // uint8 [E][16] quadratic-patch-local ids of the 10 nodes (padded to 16 bytes)
   ebe::DBuf lconn1;     // uint8 [E][4]  linear-patch-local ids of the 4 corners
   ebe::PatchLevel pl[2];
+  // fans of the quadratic patches; empty on meshes of 2^25 nodes or more and on curved ones
+  ebe::DBuf pfan;       // int32 [npatch+1] fan offsets
+  ebe::DBuf fanw;       // uint32 [nfan][kFanStride]
+  ebe::DBuf felem;      // int32 [nfan][kFanLen] element, -1: none
+  int64_t nfan = 0;
   ebe::DBuf gacc;       // kGammaBytes: (x, K x) slots, then the arrival counter; zero between products
   // EBE product form per [level][dtype F64, F32][nrhs]: one of the forms, or
   // EBE_FORM_AUTO (untuned: a fixed default)
   int8_t form[2][2][EBE_MAX_RHS + 1];
-  // variant of the pipelined / coloured kernels per [level][dtype][nrhs]
-  // (0: element geometry kept in LDS, 1: read per work-item), set by the tuner
+  // kernel variant of the form per [level][dtype][nrhs], set by the tuner
   int8_t fvar[2][2][EBE_MAX_RHS + 1];
   ebe_mesh() {
     std::memset(form, EBE_FORM_AUTO, sizeof(form));
@@ -215,6 +228,10 @@ struct ebe_mesh {
   // first use by an entry point, dropped when the material changes
   ebe::DBuf geo[2];
   bool geo_ready[2] = {false, false};
+  // the same by fan tetrahedra, corners in fan order [nfan][kFanLen][16] (G_m[d] at 4 m + d,
+  // lambda V / 20 at 3, mu V / 20 at 7), for the pipelined and coloured forms of the quadratic level
+  ebe::DBuf gfan[2];
+  bool gfan_ready[2] = {false, false};
   // assembled linear-level operator K1 over the corner graph (its edges are
   // the quadratic mesh's edge nodes); structure at creation, values on demand
   ebe::AsmOp k1;
@@ -298,6 +315,7 @@ hipError_t launch_invert_blocks(const ebe_mesh* m, int level, const double* blk6
 hipError_t launch_expand_blocks(int64_t n, const double* blk6, double* out9, hipStream_t s);
 hipError_t launch_lame(const ebe_mesh* m, hipStream_t s);
 hipError_t launch_geometry(const ebe_mesh* m, ebe_dtype dt, void* out, hipStream_t s);
+hipError_t launch_fan_geometry(const ebe_mesh* m, ebe_dtype dt, void* out, hipStream_t s);
 // K1 of the linear (corner) mesh into k1.val[0] (FP64, atomics into zeroed
 // blocks), and its FP32 copy into k1.val[1] when f32 is set
 // assemble: form the FP64 values (zeroed first); f32: copy them to the FP32 values
@@ -330,6 +348,8 @@ ebe_status ensure_blocks(ebe_mesh* m, hipStream_t s);
 // fill the geometry cache of dtype dt if needed (allocates: call before any
 // graph capture; every entry point that launches products does)
 ebe_status ensure_geometry(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
+// the same for the fan-ordered rows
+ebe_status ensure_fan_geometry(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
 // build the assembled linear-level operator of dtype dt if needed (allocates)
 ebe_status ensure_assembled(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
 // everything products of (level, dtype, nrhs) in their current form need:

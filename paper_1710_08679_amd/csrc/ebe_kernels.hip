@@ -540,13 +540,11 @@ hipError_t ebe_dispatch_p(int order, int form, const ebe_mesh* m, const void* x,
     return launch_asm_p<T, NR>(m, m->k1, fx, x, y, mask_in, bc, add, gate, s, gamma);
   }
   if (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED) {
-    const bool colour = form == EBE_FORM_COLOURED;
-    const int var = m->fvar[order == 2 ? 0 : 1][sizeof(T) == 8 ? 0 : 1][NR];
     if (order == 2)
-      return var != 1 ? launch_pipe<T, NR, 2, true, 1>(m, x, y, mask_in, bc, add, gate, s, gamma, colour)
-                      : launch_pipe<T, NR, 2, false, 1>(m, x, y, mask_in, bc, add, gate, s, gamma, colour);
-    return var != 1 ? launch_pipe<T, NR, 1, true, 1>(m, x, y, mask_in, bc, add, gate, s, gamma, colour)
-                    : launch_pipe<T, NR, 1, false, 1>(m, x, y, mask_in, bc, add, gate, s, gamma, colour);
+      return launch_fan<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma, form == EBE_FORM_COLOURED);
+    return m->fvar[1][sizeof(T) == 8 ? 0 : 1][NR] != 1
+               ? launch_pipe<T, NR, true>(m, x, y, mask_in, bc, add, gate, s, gamma)
+               : launch_pipe<T, NR, false>(m, x, y, mask_in, bc, add, gate, s, gamma);
   }
   // stream the staged partials past the caches when they cannot stay in the
   // last-level cache until the shared-node pass reads them back
@@ -693,7 +691,7 @@ bool form_usable(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs)
   // node tables hold 32-bit byte offsets of node rows
   const int64_t rows = order == 2 ? m->n_nodes : m->n_vertices;
   const int64_t row_bytes = int64_t(3) * nrhs * (dt == EBE_F64 ? 8 : 4);
-  if (L.ptab.bytes() == 0 || rows * row_bytes >= (int64_t(1) << 32)) return false;
+  if ((order == 2 ? m->nfan == 0 : L.ptab.bytes() == 0) || rows * row_bytes >= (int64_t(1) << 32)) return false;
   return form != EBE_FORM_COLOURED || L.coff.size() > 1;
 }
 
@@ -712,7 +710,7 @@ hipError_t launch_ebe_form(const ebe_mesh* m, int order, int form, ebe_dtype dt,
   if ((staged && L.stage.bytes() < need) || L.npatch < 1 || nrhs < 1 || nrhs > EBE_MAX_RHS ||
       !form_usable(m, order, form, dt, nrhs) ||
       ((form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED || form == EBE_FORM_DETERMINISTIC) &&
-       !m->geo_ready[k]) ||
+       !(order == 2 && form != EBE_FORM_DETERMINISTIC ? m->gfan_ready[k] : m->geo_ready[k])) ||
       (form == EBE_FORM_ASSEMBLED && !m->k1.ready[k]))
     return hipErrorInvalidValue;  // staging, geometry or assembled values not prepared, or bad form: host bug
   if (form == EBE_FORM_DETERMINISTIC)

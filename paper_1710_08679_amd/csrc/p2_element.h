@@ -172,8 +172,10 @@ EBE_HD void p2_apply(const T G[4][3], T cl, T cm, U&& u, Emit&& emit, bool with_
     fma_eng(w[k], ue, G[m]);
     fma_eng(w[m], ue, G[k]);
   }
-  // S'_k from the strain 4 w_k - A (w is overwritten by S'_k)
-  T Ssum[6], esum[6];
+  // S'_k from the strain 4 w_k - A (w is overwritten by S'_k).  With the
+  // energy, the strains' sum is kept and S' formed from it at the end (S is
+  // linear in e), so no second sum is live
+  T Ssum[6];
   T en = T(0);
   const T cm2 = cm + cm;
 #pragma unroll
@@ -189,18 +191,20 @@ EBE_HD void p2_apply(const T G[4][3], T cl, T cm, U&& u, Emit&& emit, bool with_
     w[k][4] = cm * e[4];
     w[k][5] = cm * e[5];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) Ssum[c] = (k == 0) ? w[k][c] : Ssum[c] + w[k][c];
-    if (with_energy) {
-#pragma unroll
-      for (int c = 0; c < 6; ++c) {
-        en += w[k][c] * e[c];
-        esum[c] = (k == 0) ? e[c] : esum[c] + e[c];
-      }
+    for (int c = 0; c < 6; ++c) {
+      const T v = with_energy ? e[c] : w[k][c];
+      Ssum[c] = (k == 0) ? v : Ssum[c] + v;
+      if (with_energy) en += w[k][c] * e[c];
     }
   }
   if (with_energy) {
+    const T clt = cl * ((Ssum[0] + Ssum[1]) + Ssum[2]);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) en += Ssum[c] * esum[c];
+    for (int c = 0; c < 6; ++c) {
+      const T ec = Ssum[c];
+      Ssum[c] = c < 3 ? cm2 * ec + clt : cm * ec;
+      en += Ssum[c] * ec;
+    }
     energy = en;
   }
   // corners: f_i = (4 S'_i - S') G_i

@@ -14,6 +14,8 @@
 // so its workgroups need more elements to carry the fixed cost of a patch.
 #include <algorithm>
 #include <cstring>
+#include <exception>
+#include <thread>
 #include <vector>
 
 #include "ebe_internal.h"
@@ -21,6 +23,30 @@
 namespace ebe {
 
 namespace {
+
+// f(0) .. f(n - 1), each on a thread of its own; the first exception is rethrown after all have ended
+template <class F>
+void parallel(int n, F f) {
+  std::vector<std::exception_ptr> err(n);
+  std::vector<std::thread> threads;
+  auto run = [&](int t) {
+    try {
+      f(t);
+    } catch (...) {
+      err[t] = std::current_exception();
+    }
+  };
+  int started = 1;  // f(0) runs here, and what no thread could be started for
+  try {
+    for (; started < n; ++started) threads.emplace_back(run, started);
+  } catch (...) {
+  }
+  run(0);
+  for (int t = started; t < n; ++t) run(t);
+  for (auto& t : threads) t.join();
+  for (auto& e : err)
+    if (e) std::rethrow_exception(e);
+}
 
 struct LevelTables {
   std::vector<int32_t> poff, pnode, pslot;      // per patch entries
@@ -122,6 +148,169 @@ std::vector<uint32_t> node_words(int64_t E, int nloc, NodeOf node_of, const std:
   return w;
 }
 
+// A fan: a chain of at most kFanLen tetrahedra of a patch around a common edge
+// (p, q), each sharing a face with the next.  corner[i]: element-local corners
+// (p, q, spoke i, spoke i + 1), an even permutation of the element's own order,
+// so the orientation stays positive.
+struct Fan {
+  int32_t len = 0;
+  int32_t elem[kFanLen];
+  uint8_t corner[kFanLen][4];
+};
+
+// element-local corners of the ends of each edge and of the other two, as even permutations
+const uint8_t kEdgePerm[6][4] = {{0, 1, 2, 3}, {1, 2, 0, 3}, {0, 2, 3, 1}, {0, 3, 1, 2}, {1, 3, 2, 0}, {2, 3, 0, 1}};
+// edge node between two local corners
+const int kEdgeNode[4][4] = {{-1, 4, 6, 7}, {4, -1, 5, 8}, {6, 5, -1, 9}, {7, 8, 9, -1}};
+
+// Groups elements [e0, e0 + ne) into fans: each element not yet in one, in
+// order, seeds the longest fan any of its six edges allows (ties: the lowest
+// element numbers, which in a Kuhn lattice keeps a hexahedron's six
+// tetrahedra, a ring around its diagonal, in two fans of three).
+void fans_of_patch(int32_t e0, int32_t ne, const int32_t* conn10, std::vector<Fan>& out) {
+  struct Face {
+    int32_t v[3];  // corners, increasing
+    int32_t el;
+    uint8_t opposite;  // the element's local corner off the face
+  };
+  std::vector<Face> faces;
+  faces.reserve(size_t(ne) * 4);
+  for (int32_t el = 0; el < ne; ++el) {
+    const int32_t* c = conn10 + size_t(e0 + el) * 10;
+    for (int o = 0; o < 4; ++o) {
+      Face f{};
+      int n = 0;
+      for (int k = 0; k < 4; ++k)
+        if (k != o) f.v[n++] = c[k];
+      std::sort(f.v, f.v + 3);
+      f.el = el;
+      f.opposite = uint8_t(o);
+      faces.push_back(f);
+    }
+  }
+  std::sort(faces.begin(), faces.end(), [](const Face& a, const Face& b) {
+    for (int k = 0; k < 3; ++k)
+      if (a.v[k] != b.v[k]) return a.v[k] < b.v[k];
+    return a.el < b.el;
+  });
+  // across[el * 4 + o]: neighbour over the face opposite local corner o, as element * 4 + its opposite corner
+  std::vector<int32_t> across(size_t(ne) * 4, -1);
+  for (size_t i = 0; i + 1 < faces.size(); ++i) {
+    const Face &a = faces[i], &b = faces[i + 1];
+    if (std::equal(a.v, a.v + 3, b.v)) {
+      across[size_t(a.el) * 4 + a.opposite] = b.el * 4 + b.opposite;
+      across[size_t(b.el) * 4 + b.opposite] = a.el * 4 + a.opposite;
+    }
+  }
+  struct Link {
+    int32_t el;
+    uint8_t c[4];
+  };
+  // the neighbour n (element * 4 + opposite corner) of t over the face of p, q
+  // and t's spoke t.c[keep], as a link; false if its corners would not be an even permutation
+  auto link = [&](const Link& t, int keep, int32_t n, Link& l) {
+    const int32_t* ct = conn10 + size_t(e0 + t.el) * 10;
+    const int32_t* cn = conn10 + size_t(e0 + n / 4) * 10;
+    l.el = n / 4;
+    const int from[3] = {0, 1, keep}, to[3] = {0, 1, keep == 3 ? 2 : 3};
+    l.c[keep == 3 ? 3 : 2] = uint8_t(n % 4);
+    for (int i = 0; i < 3; ++i)
+      l.c[to[i]] = uint8_t(std::find(cn, cn + 4, ct[t.c[from[i]]]) - cn);
+    int inv = 0;
+    for (int i = 0; i < 4; ++i)
+      for (int j = i + 1; j < 4; ++j) inv += l.c[i] > l.c[j];
+    return (inv & 1) == 0;
+  };
+  std::vector<uint8_t> used(ne, 0);
+  for (int32_t el = 0; el < ne; ++el) {
+    if (used[el]) continue;
+    Fan best;
+    int64_t best_sum = 0;
+    for (const auto& perm : kEdgePerm) {
+      Link chain[2 * kFanLen];
+      int lo = kFanLen, hi = kFanLen;
+      chain[lo] = Link{el, {perm[0], perm[1], perm[2], perm[3]}};
+      auto extend = [&](const Link& t, int keep, Link& l) {
+        const int32_t n = across[size_t(t.el) * 4 + t.c[keep == 3 ? 2 : 3]];
+        if (n < 0 || used[n / 4]) return false;
+        for (int i = lo; i <= hi; ++i)
+          if (chain[i].el == n / 4) return false;
+        return link(t, keep, n, l);
+      };
+      while (hi - lo + 1 < kFanLen && extend(chain[hi], 3, chain[hi + 1])) ++hi;
+      while (hi - lo + 1 < kFanLen && extend(chain[lo], 2, chain[lo - 1])) --lo;
+      const int len = hi - lo + 1;
+      int64_t sum = 0;
+      for (int i = lo; i <= hi; ++i) sum += chain[i].el;
+      if (len > best.len || (len == best.len && sum < best_sum)) {
+        best.len = len;
+        best_sum = sum;
+        for (int i = 0; i < len; ++i) {
+          best.elem[i] = e0 + chain[lo + i].el;
+          std::copy(chain[lo + i].c, chain[lo + i].c + 4, best.corner[i]);
+        }
+      }
+    }
+    for (int i = 0; i < best.len; ++i) used[best.elem[i] - e0] = 1;
+    out.push_back(best);
+  }
+}
+
+// Fan tables of all patches (long fans first within a patch, so a wavefront's
+// fans have like lengths), patches spread over a few host threads.
+void build_fans(const std::vector<int32_t>& pelem, const int32_t* conn10, const std::vector<uint8_t>& lconn,
+                const uint8_t* fix, std::vector<int32_t>& pfan, std::vector<uint32_t>& fanw,
+                std::vector<int32_t>& felem) {
+  const int64_t npatch = int64_t(pelem.size()) - 1;
+  const int nthread = int(std::max<int64_t>(1, std::min<int64_t>({8, int64_t(std::thread::hardware_concurrency()),
+                                                                   npatch / 256})));
+  std::vector<std::vector<Fan>> part(nthread);
+  pfan.assign(npatch + 1, 0);
+  auto first = [&](int t) { return npatch * t / nthread; };
+  parallel(nthread, [&](int t) {
+    for (int64_t p = first(t); p < first(t + 1); ++p) {
+      const size_t f0 = part[t].size();
+      fans_of_patch(pelem[p], pelem[p + 1] - pelem[p], conn10, part[t]);
+      std::stable_sort(part[t].begin() + f0, part[t].end(), [](const Fan& a, const Fan& b) { return a.len > b.len; });
+      pfan[p + 1] = int32_t(part[t].size() - f0);
+    }
+  });
+  for (int64_t p = 0; p < npatch; ++p) pfan[p + 1] += pfan[p];
+  fanw.assign(size_t(pfan[npatch]) * kFanStride, 0);
+  felem.assign(size_t(pfan[npatch]) * kFanLen, -1);
+  parallel(nthread, [&](int t) {
+    size_t f = size_t(pfan[first(t)]);
+    for (const Fan& fan : part[t]) {
+      uint32_t* w = &fanw[f * kFanStride];
+      auto put = [&](int a, int32_t e, int local) {
+        const int32_t v = conn10[size_t(e) * 10 + local];
+        w[a] = uint32_t(v) | (uint32_t(lconn[size_t(e) * 16 + local]) << kPtabLocalShift);
+        if (a < 10) w[kFanWords] |= uint32_t(fix[v]) << (2 + 3 * a);
+        else w[kFanWords + 1] |= uint32_t(fix[v]) << (3 * (a - 10));
+      };
+      w[kFanWords] = uint32_t(fan.len);
+      for (int i = 0; i < fan.len; ++i) {
+        const int32_t e = fan.elem[i];
+        const uint8_t* c = fan.corner[i];
+        felem[f * kFanLen + i] = e;
+        if (i == 0) {
+          put(0, e, c[0]);
+          put(1, e, c[1]);
+          put(2, e, kEdgeNode[c[0]][c[1]]);
+          put(3, e, c[2]);
+          put(4, e, kEdgeNode[c[0]][c[2]]);
+          put(5, e, kEdgeNode[c[1]][c[2]]);
+        }
+        put(6 + 4 * i, e, c[3]);
+        put(7 + 4 * i, e, kEdgeNode[c[0]][c[3]]);
+        put(8 + 4 * i, e, kEdgeNode[c[1]][c[3]]);
+        put(9 + 4 * i, e, kEdgeNode[c[2]][c[3]]);
+      }
+      ++f;
+    }
+  });
+}
+
 // Greedy colouring of the patches (in patch order, each takes the smallest
 // colour no patch sharing a node with it has), the patches listed colour by
 // colour, and the node words with bit 31 set where an earlier patch in that
@@ -204,10 +393,8 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
   ebe_status st = EBE_OK;
   if ((st = up(m->lconn, lconn, s)) != EBE_OK) return st;
   if ((st = up(m->lconn1, lconn1, s)) != EBE_OK) return st;
-  if (m->n_nodes <= int64_t(kPtabIdMask)) {  // element node words (pipelined and coloured forms)
-    if ((st = up(m->pl[0].ptab, node_words(E, 10, node_of, lconn, 16), s)) != EBE_OK) return st;
+  if (m->n_nodes <= int64_t(kPtabIdMask))  // element node words (pipelined form of the linear level)
     if ((st = up(m->pl[1].ptab, node_words(E, 4, node_of, lconn1, 4), s)) != EBE_OK) return st;
-  }
   {
     std::vector<int32_t> cperm, cword;
     colour_patches(m->n_nodes, t[0], cperm, m->pl[0].coff, cword);
@@ -237,6 +424,15 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
     }
     if ((st = up(m->pl[0].pinc, pinc, s)) != EBE_OK) return st;
     if ((st = up(m->pl[0].pistart, pistart, s)) != EBE_OK) return st;
+  }
+  if (m->n_nodes <= int64_t(kPtabIdMask) && !m->curved) {  // fans (pipelined and coloured forms)
+    std::vector<int32_t> pfan, felem;
+    std::vector<uint32_t> fanw;
+    build_fans(pelem[0], conn10, lconn, fix, pfan, fanw, felem);
+    m->nfan = int64_t(felem.size()) / kFanLen;
+    if ((st = up(m->pfan, pfan, s)) != EBE_OK) return st;
+    if ((st = up(m->fanw, fanw, s)) != EBE_OK) return st;
+    if ((st = up(m->felem, felem, s)) != EBE_OK) return st;
   }
   for (int l = 0; l < 2; ++l) {
     PatchLevel& L = m->pl[l];

@@ -231,6 +231,40 @@ __global__ __launch_bounds__(kBlock) void k_geometry(const int32_t* __restrict__
   o[15] = T(0);
 }
 
+// The same for the tetrahedra of the fans (corners p, q, spoke k, spoke k + 1),
+// rows of 16 values: gradient m's component d at 4 m + d, lambda V / 20 at 3,
+// mu V / 20 at 7; zero where a fan has fewer tetrahedra.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_fan_geometry(const uint32_t* __restrict__ fanw,
+                                                         const int32_t* __restrict__ felem,
+                                                         const double4* __restrict__ xv,
+                                                         const double2* __restrict__ lame, T* __restrict__ out,
+                                                         int64_t n) {
+  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  if (i >= n) return;
+  T* o = out + i * 16;
+  const int32_t e = felem[i];
+  if (e < 0) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) o[k] = T(0);
+    return;
+  }
+  const int64_t f = i / kFanLen;
+  const int k = int(i - f * kFanLen);
+  const uint32_t* w = fanw + f * kFanStride;
+  T G[4][3];
+  const T V = tet_geometry<T>(xv[w[0] & kPtabIdMask], xv[w[1] & kPtabIdMask],
+                              xv[w[k == 0 ? 3 : 2 + 4 * k] & kPtabIdMask], xv[w[6 + 4 * k] & kPtabIdMask], G);
+  const double2 lm = lame[e];
+  const T s = V * T(0.05);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) o[4 * m + d] = G[m][d];
+    o[4 * m + 3] = m == 0 ? T(lm.x) * s : (m == 1 ? T(lm.y) * s : T(0));
+  }
+}
+
 // Level-2 prolongator P2 = (I - omega D1^-1 K1p) T, one work-item per fine
 // row v: slot w of the row (aggregate J) is [J = agg(v)] I_free(v)
 // - omega D1^-1(v) sum_{b in row v of K1, agg(b) = J} K1p(v, b), with K1p's
@@ -572,6 +606,19 @@ hipError_t launch_geometry(const ebe_mesh* m, ebe_dtype dt, void* out, hipStream
   else
     hipLaunchKernelGGL(k_geometry<float>, dim3(grid_for(m->n_elem)), dim3(kBlock), 0, s, m->conn.as<int32_t>(),
                        m->xv.as<double4>(), m->lame64.as<double2>(), static_cast<float*>(out), m->n_elem);
+  return hipGetLastError();
+}
+
+hipError_t launch_fan_geometry(const ebe_mesh* m, ebe_dtype dt, void* out, hipStream_t s) {
+  const int64_t n = m->nfan * kFanLen;
+  if (dt == EBE_F64)
+    hipLaunchKernelGGL(k_fan_geometry<double>, dim3(grid_for(n)), dim3(kBlock), 0, s, m->fanw.as<uint32_t>(),
+                       m->felem.as<int32_t>(), m->xv.as<double4>(), m->lame64.as<double2>(),
+                       static_cast<double*>(out), n);
+  else
+    hipLaunchKernelGGL(k_fan_geometry<float>, dim3(grid_for(n)), dim3(kBlock), 0, s, m->fanw.as<uint32_t>(),
+                       m->felem.as<int32_t>(), m->xv.as<double4>(), m->lame64.as<double2>(),
+                       static_cast<float*>(out), n);
   return hipGetLastError();
 }
 

@@ -1,0 +1,68 @@
+"""Quadratic products whose patches group into few or short fans.
+
+The pipelined and coloured forms take the tetrahedra of a patch in fans (up
+to three around a common edge).  A lattice in its own order has sixteen full
+fans to a patch; here the elements come in other orders, so that fans of one
+and two tetrahedra occur, and patches of more fans than the kernel's tables
+hold at once.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fem
+from paper_1710_08679_amd import ebe, meshgen
+from tests.helpers import assert_close_bound, kappa_max, oracle_K, parity_mesh
+
+pytestmark = pytest.mark.gpu
+
+DT = {np.float64: torch.float64, np.float32: torch.float32}
+
+
+def reordered(m, order):
+    m.conn, m.young, m.poisson = m.conn[order].copy(), m.young[order].copy(), m.poisson[order].copy()
+    return m
+
+
+def checkered(m):
+    """First the even tetrahedra of the hexahedra of one parity and the odd
+    ones of the others (no two of these share a face: every fan is a single
+    tetrahedron, 24 of them to a block of eight hexahedra), then the rest."""
+    hexes = np.floor(m.refined[m.conn].min(axis=1) / 2).astype(int).sum(axis=1)
+    v = m.refined[m.conn[:, :4]].astype(int)
+    # the first step of a tetrahedron's path from its lowest to its highest corner, and the second
+    path = np.argsort(v.sum(axis=2), axis=1)
+    e = np.arange(m.n_elem)
+    s1 = np.argmax(v[e, path[:, 1]] - v[e, path[:, 0]], axis=1)
+    s2 = np.argmax(v[e, path[:, 2]] - v[e, path[:, 1]], axis=1)
+    even = (s2 - s1) % 3 == 1
+    first = even == (hexes % 2 == 0)
+    return reordered(m, np.concatenate([np.nonzero(first)[0], np.nonzero(~first)[0]]))
+
+
+def interleaved(m):
+    """Every second tetrahedron, then the others: mostly fans of two."""
+    return reordered(m, np.concatenate([np.arange(0, m.n_elem, 2), np.arange(1, m.n_elem, 2)]))
+
+
+@pytest.fixture(scope="module", params=["checkered", "interleaved"])
+def case(request, gpu_lib):
+    m = parity_mesh(4, 4, 4, seed=5, bc=True)
+    m = checkered(m) if request.param == "checkered" else interleaved(m)
+    return m, ebe.Mesh.from_generated(m), oracle_K(m), kappa_max(m)
+
+
+@pytest.mark.parametrize("form", [ebe.FORM_PIPELINED, ebe.FORM_COLOURED])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nrhs", [1, 5, 12, 16])
+def test_products_of_short_fans(case, dtype, nrhs, form):
+    m, gm, K, kap = case
+    x = meshgen.rng_for(91, nrhs).standard_normal((m.n_nodes, 3, nrhs)).astype(dtype)
+    gm.set_form(0, DT[dtype], nrhs, form)
+    xr = x.astype(np.float64)
+    xd = torch.from_numpy(x).cuda()
+    y = gm.matvec(xd).cpu().numpy().astype(np.float64)
+    ref = (K @ xr.reshape(-1, nrhs)).reshape(y.shape)
+    assert_close_bound(y, ref, abs(K), xr, dtype, kap, f"K x n={nrhs} form={form}")
+    yb = gm.matvec(xd, apply_bc=True).cpu().numpy().astype(np.float64)
+    assert_close_bound(yb, fem.matvec_bc(K, xr, m.fixed), abs(K), xr, dtype, kap, f"P K P x n={nrhs} form={form}")
