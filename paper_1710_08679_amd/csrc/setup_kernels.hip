@@ -207,6 +207,23 @@ __global__ __launch_bounds__(kBlock) void k_lame(const double* __restrict__ E,
   l32[i] = make_float2(float(lam), float(mu));
 }
 
+// a geometry row of 16 values, in 16-byte stores
+template <typename T>
+__device__ __forceinline__ void store_row(T* __restrict__ out, const T o[16]) {
+  struct alignas(16) Piece {
+    T v[16 / sizeof(T)];
+  };
+  constexpr int GV = 16 / int(sizeof(T));
+#pragma unroll
+  for (int p = 0; p < 16 / GV; ++p) {
+    Piece q;
+#pragma unroll
+    for (int t = 0; t < GV; ++t) q.v[t] = o[p * GV + t];
+    reinterpret_cast<Piece*>(out)[p] = q;
+  }
+}
+
+
 // Geometry cache row of element i: barycentric gradients G (4 x 3), volume
 // V, lambda, mu (then padding to 16 values), formed exactly as the patch
 // kernels form them from the corner coordinates.
@@ -219,7 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_geometry(const int32_t* __restrict__
   T G[4][3];
   const T V = tet_geometry<T>(xv[conn[i * 10 + 0] & kIdxMask], xv[conn[i * 10 + 1] & kIdxMask],
                               xv[conn[i * 10 + 2] & kIdxMask], xv[conn[i * 10 + 3] & kIdxMask], G);
-  T* o = out + i * 16;
+  T o[16];
 #pragma unroll
   for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -229,6 +246,7 @@ __global__ __launch_bounds__(kBlock) void k_geometry(const int32_t* __restrict__
   o[13] = T(lm.x);
   o[14] = T(lm.y);
   o[15] = T(0);
+  store_row(out + i * 16, o);
 }
 
 // The same for the tetrahedra of the fans (corners p, q, spoke k, spoke k + 1),
@@ -242,11 +260,12 @@ __global__ __launch_bounds__(kBlock) void k_fan_geometry(const uint32_t* __restr
                                                          int64_t n) {
   const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   if (i >= n) return;
-  T* o = out + i * 16;
+  T o[16];
   const int32_t e = felem[i];
   if (e < 0) {
 #pragma unroll
     for (int k = 0; k < 16; ++k) o[k] = T(0);
+    store_row(out + i * 16, o);
     return;
   }
   const int64_t f = i / kFanLen;
@@ -263,6 +282,7 @@ __global__ __launch_bounds__(kBlock) void k_fan_geometry(const uint32_t* __restr
     for (int d = 0; d < 3; ++d) o[4 * m + d] = G[m][d];
     o[4 * m + 3] = m == 0 ? T(lm.x) * s : (m == 1 ? T(lm.y) * s : T(0));
   }
+  store_row(out + i * 16, o);
 }
 
 // Level-2 prolongator P2 = (I - omega D1^-1 K1p) T, one work-item per fine
