@@ -142,10 +142,10 @@ ebe_status ensure_half(ebe_mesh* m, int level, hipStream_t s) {
 ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s) {
   ebe_status st = ensure_stage(m, nrhs, dt == EBE_F64 ? 8 : 4);
   const int form = product_form(m, level == 0 ? 2 : 1, dt, nrhs);
-  if (st == EBE_OK && level == 0 && (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED))
-    st = ensure_fan_geometry(m, dt, s);
-  else if (st == EBE_OK)
-    st = ensure_geometry(m, dt, s);
+  // (both geometry caches, whichever the form reads: after one product another
+  // form can be set and captured into a graph without an allocation)
+  if (st == EBE_OK) st = ensure_geometry(m, dt, s);
+  if (st == EBE_OK && level == 0) st = ensure_fan_geometry(m, dt, s);
   if (st == EBE_OK && level == 1 && form == EBE_FORM_ASSEMBLED) st = ensure_assembled(m, dt, s);
   return st;
 }
