@@ -39,19 +39,15 @@ EBE_HD constexpr int edge_end(int q, int side) {
                    : (q == 0 ? 1 : q == 1 ? 2 : q == 2 ? 2 : 3);
 }
 
-// Barycentric gradients G[4][3] and volume of the corner tetrahedron.  Edge
-// vectors are formed in FP64 (coordinates are FP64), the rest in T.
+// Barycentric gradients G[4][3] and volume of a tetrahedron from its edge
+// vectors a, b, c (corners 1, 2, 3 minus corner 0).
 template <typename T>
-EBE_HD T tet_geometry(const double4& p0, const double4& p1, const double4& p2,
-                                          const double4& p3, T G[4][3]) {
-  const T a0 = T(p1.x - p0.x), a1 = T(p1.y - p0.y), a2 = T(p1.z - p0.z);
-  const T b0 = T(p2.x - p0.x), b1 = T(p2.y - p0.y), b2 = T(p2.z - p0.z);
-  const T c0 = T(p3.x - p0.x), c1 = T(p3.y - p0.y), c2 = T(p3.z - p0.z);
+EBE_HD T tet_geometry(const T a[3], const T b[3], const T c[3], T G[4][3]) {
   // rows of the inverse Jacobian: (b x c, c x a, a x b) / det
-  const T bc0 = b1 * c2 - b2 * c1, bc1 = b2 * c0 - b0 * c2, bc2 = b0 * c1 - b1 * c0;
-  const T ca0 = c1 * a2 - c2 * a1, ca1 = c2 * a0 - c0 * a2, ca2 = c0 * a1 - c1 * a0;
-  const T ab0 = a1 * b2 - a2 * b1, ab1 = a2 * b0 - a0 * b2, ab2 = a0 * b1 - a1 * b0;
-  const T det = a0 * bc0 + a1 * bc1 + a2 * bc2;
+  const T bc0 = b[1] * c[2] - b[2] * c[1], bc1 = b[2] * c[0] - b[0] * c[2], bc2 = b[0] * c[1] - b[1] * c[0];
+  const T ca0 = c[1] * a[2] - c[2] * a[1], ca1 = c[2] * a[0] - c[0] * a[2], ca2 = c[0] * a[1] - c[1] * a[0];
+  const T ab0 = a[1] * b[2] - a[2] * b[1], ab1 = a[2] * b[0] - a[0] * b[2], ab2 = a[0] * b[1] - a[1] * b[0];
+  const T det = a[0] * bc0 + a[1] * bc1 + a[2] * bc2;
   const T inv = T(1) / det;
   G[1][0] = bc0 * inv; G[1][1] = bc1 * inv; G[1][2] = bc2 * inv;
   G[2][0] = ca0 * inv; G[2][1] = ca1 * inv; G[2][2] = ca2 * inv;
@@ -59,6 +55,17 @@ EBE_HD T tet_geometry(const double4& p0, const double4& p1, const double4& p2,
 #pragma unroll
   for (int d = 0; d < 3; ++d) G[0][d] = -(G[1][d] + G[2][d] + G[3][d]);
   return det * T(1.0 / 6.0);
+}
+
+// The same from the corners.  Edge vectors are formed in FP64 (coordinates
+// are FP64), the rest in T.
+template <typename T>
+EBE_HD T tet_geometry(const double4& p0, const double4& p1, const double4& p2,
+                                          const double4& p3, T G[4][3]) {
+  const T a[3] = {T(p1.x - p0.x), T(p1.y - p0.y), T(p1.z - p0.z)};
+  const T b[3] = {T(p2.x - p0.x), T(p2.y - p0.y), T(p2.z - p0.z)};
+  const T c[3] = {T(p3.x - p0.x), T(p3.y - p0.y), T(p3.z - p0.z)};
+  return tet_geometry<T>(a, b, c, G);
 }
 
 // w += engineering strain of the outer product d (x) g

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import fem
+from oracle import adjoint, fem
 from paper_1710_08679_amd import ebe, meshgen
 from tests.helpers import assert_close_bound, kappa_max, oracle_K, parity_mesh
 
@@ -66,3 +66,15 @@ def test_products_of_short_fans(case, dtype, nrhs, form):
     assert_close_bound(y, ref, abs(K), xr, dtype, kap, f"K x n={nrhs} form={form}")
     yb = gm.matvec(xd, apply_bc=True).cpu().numpy().astype(np.float64)
     assert_close_bound(yb, fem.matvec_bc(K, xr, m.fixed), abs(K), xr, dtype, kap, f"P K P x n={nrhs} form={form}")
+
+
+@pytest.mark.parametrize("dtype, tol", [(np.float64, 1e-12), (np.float32, 2e-5)])
+@pytest.mark.parametrize("nrhs", [1, 3, 4, 7, 11, 16])
+def test_adjoint_gradient_of_short_fans(case, dtype, tol, nrhs):
+    m, gm, _, _ = case
+    rng = meshgen.rng_for(92, nrhs)
+    u, lam = (rng.standard_normal((m.n_nodes, 3, nrhs)).astype(dtype) for _ in range(2))
+    free = 1.0 - m.fixed[:, :, None].astype(np.float64)
+    ref = adjoint.element_gradient(m.xyz, m.conn, m.poisson, u * free, lam * free)
+    g = gm.adjoint_grad(torch.from_numpy(u).cuda(), torch.from_numpy(lam).cuda()).cpu().numpy()
+    assert np.max(np.abs(g - ref)) <= tol * np.max(np.abs(ref))
