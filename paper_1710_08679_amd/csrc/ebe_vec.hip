@@ -127,28 +127,39 @@ __global__ __launch_bounds__(kBlock) void k_prolong_p2(const int32_t* __restrict
 }
 
 // y[Na] = P2^T x[Nv]: for aggregate I, the P2 entries naming it (fine rows in
-// increasing order), each block transposed; zero at fixed coarse DOFs
+// increasing order), each block transposed; zero at fixed coarse DOFs.  One
+// workgroup per aggregate: work-item (s, vector of the row) adds entries s,
+// s + SPL, ... in FP64, then the SPL partial rows are added in order.  (One
+// work-item per vector of a row walking all of an aggregate's about 100
+// entries left the chip nearly empty: 109 us on the 48x48x24 crust's 3,075
+// aggregates at FP32, 16 cases.)
+template <typename T, int NR>
+constexpr int p2t_splits() {
+  return kBlock / (3 * NR / xfer_vec<T, NR>());
+}
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) void k_restrict_p2(const int32_t* __restrict__ toff,
                                                         const int32_t* __restrict__ tidx, int width,
                                                         const T* __restrict__ pval, const uint8_t* __restrict__ cfix,
-                                                        const T* __restrict__ x, T* __restrict__ y, int64_t na) {
-  constexpr int VW = xfer_vec<T, NR>(), W = 3 * NR, PR = W / VW;
+                                                        const T* __restrict__ x, T* __restrict__ y) {
+  constexpr int VW = xfer_vec<T, NR>(), W = 3 * NR, PR = W / VW, SPL = p2t_splits<T, NR>();
   using V = VecT<T, VW>;
-  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= na * PR) return;
-  const int64_t a = i / PR;
-  const int off = int(i - a * PR) * VW;
-  const int q = off / NR, j = off - q * NR;
+  __shared__ double part[SPL][PR][VW];
+  const int64_t a = blockIdx.x;
+  const int s = int(threadIdx.x) / PR, o = int(threadIdx.x) - s * PR;
+  const int off = o * VW, q = off / NR, j = off - q * NR;
+  const bool fixed = (cfix[a] >> q) & 1;
   double acc[VW];
 #pragma unroll
   for (int t = 0; t < VW; ++t) acc[t] = 0.0;
-  if (!((cfix[a] >> q) & 1))
-    for (int32_t k = toff[a]; k < toff[a + 1]; ++k) {
-      const int64_t e = tidx[k];
-      const int64_t v = e / width;
-      const T* b = pval + e * 9 + q;
-      const T* xs = x + v * W + j;
+  if (s < SPL && !fixed) {
+    const int32_t k1 = toff[a + 1];
+#pragma unroll 2
+    for (int32_t k = toff[a] + s; k < k1; k += SPL) {
+      const uint32_t e = uint32_t(tidx[k]);
+      const uint32_t v = e / uint32_t(width);
+      const T* b = pval + size_t(e) * 9 + q;
+      const T* xs = x + size_t(v) * W + j;
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
         const V xv = *reinterpret_cast<const V*>(xs + p * NR);
@@ -157,10 +168,21 @@ __global__ __launch_bounds__(kBlock) void k_restrict_p2(const int32_t* __restric
         for (int t = 0; t < VW; ++t) acc[t] += bp * double(xv.v[t]);
       }
     }
-  V out;
+  }
+  if (s < SPL) {
 #pragma unroll
-  for (int t = 0; t < VW; ++t) out.v[t] = T(acc[t]);
-  *reinterpret_cast<V*>(y + a * W + off) = out;
+    for (int t = 0; t < VW; ++t) part[s][o][t] = acc[t];
+  }
+  __syncthreads();
+  if (s == 0) {
+    for (int i = 1; i < SPL; ++i)
+#pragma unroll
+      for (int t = 0; t < VW; ++t) acc[t] += part[i][o][t];
+    V out;
+#pragma unroll
+    for (int t = 0; t < VW; ++t) out.v[t] = T(acc[t]);
+    *reinterpret_cast<V*>(y + a * W + off) = out;
+  }
 }
 
 // y = M^-1 x with symmetric inverse blocks (xx yy zz yz zx xy)
@@ -215,9 +237,9 @@ hipError_t xfer_p(int which, const ebe_mesh* m, const void* x, void* y, bool bc,
       break;
     default:  // P2^T
       if (m->n_agg < 1) return hipSuccess;
-      hipLaunchKernelGGL((k_restrict_p2<T, NR>), dim3(grid_for(m->n_agg * PR)), dim3(kBlock), 0, s,
+      hipLaunchKernelGGL((k_restrict_p2<T, NR>), dim3(unsigned(m->n_agg)), dim3(kBlock), 0, s,
                          m->p2t_off.as<int32_t>(), m->p2t_idx.as<int32_t>(), m->p2_width, m->p2_val[k].as<T>(),
-                         m->cfix.as<uint8_t>(), xs, yd, m->n_agg);
+                         m->cfix.as<uint8_t>(), xs, yd);
   }
   return hipGetLastError();
 }
