@@ -25,7 +25,7 @@ using namespace ebe;
 
 namespace {
 
-constexpr int kMaxBlocks = 1024;
+constexpr int kMaxBlocks = 256;  // workgroups that leave partial sums (solver_kernels.hip)
 
 struct Bufs {
   double *r, *p, *q;  // outer, [N][3][n] FP64

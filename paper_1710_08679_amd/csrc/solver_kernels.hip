@@ -21,9 +21,17 @@
 namespace ebe {
 namespace {
 
-constexpr int kMaxBlocks = 1024;
+// Workgroups of a node-case kernel.  With sums, at most one of 1024 work-items
+// per CU: the one-workgroup kernel that adds the partials is bound by how many
+// there are (16 cases, two sums: 8.5 us at 1024 workgroups of 256, 4.4 us at
+// 256 of 1024, the vector pass the same).  Without, two per CU (16 cases,
+// p = z + beta p averaged over the levels: 10.4 -> 8.9 us).  Systems too small
+// for that use smaller workgroups, so they still spread over the CUs.
+constexpr int kMaxThreads = 1024;
+constexpr int kMaxBlocks = 256;
+constexpr int kMaxBlocksNoSum = 512;
 
-__host__ __device__ constexpr int block_for(int nr) { return (256 / nr) * nr; }
+__host__ __device__ constexpr int block_for(int threads, int nr) { return (threads / nr) * nr; }
 
 template <typename T>
 __device__ __forceinline__ void bj_apply(const T* __restrict__ m, T x0, T x1, T x2, T& y0, T& y1, T& y2) {
@@ -45,82 +53,105 @@ __device__ __forceinline__ bool finite_d(double v) { return isfinite(v); }
 // as much as the vector work itself on the linear level.  The kernel
 // boundary makes the partials visible with one write-back.)
 template <typename Acc, int NDOT, class Body>
-__global__ __launch_bounds__(256) void k_nodecase(Body body, int64_t n_nodes, int nr, Acc* __restrict__ partials,
+__global__ __launch_bounds__(kMaxThreads) void k_nodecase(Body body, int64_t n_nodes, int nr, Acc* __restrict__ partials,
                                                   const int* __restrict__ gate) {
   if (gate && *gate == 0) return;
-  // 256 work-items per workgroup; the first bd = (256 / nr) nr of them walk
-  // the (node, case) units with a stride that is a multiple of nr, so each
-  // keeps one case; the others only join the reductions.
-  const int bd = block_for(nr);
+  // the first bd = (work-items / nr) nr walk the (node, case) units with a
+  // stride that is a multiple of nr, so each keeps one case; the others only
+  // join the reductions
+  const int threads = blockDim.x, bd = block_for(threads, nr);
   const int col = threadIdx.x % nr;
   Acc acc[NDOT > 0 ? NDOT : 1];
 #pragma unroll
   for (int d = 0; d < (NDOT > 0 ? NDOT : 1); ++d) acc[d] = Acc(0);
-  const int64_t units = n_nodes * nr;
   if (int(threadIdx.x) < bd) {
-    // four units per trip, so each work-item has four units' loads in flight
-    const int64_t stride = int64_t(gridDim.x) * bd;
-    int64_t u = int64_t(blockIdx.x) * bd + threadIdx.x;
-    for (; u + 3 * stride < units; u += 4 * stride) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) body((u + k * stride) / nr, col, acc);
+    // the stride is a multiple of nr: the node advances by a constant (one
+    // division a work-item).  Two units per trip (four took 10% longer)
+    const int64_t step = int64_t(gridDim.x) * (bd / nr);
+    int64_t node = int64_t(blockIdx.x) * (bd / nr) + int(threadIdx.x) / nr;
+#pragma unroll 1
+    for (; node + step < n_nodes; node += 2 * step) {
+      body(node, col, acc);
+      body(node + step, col, acc);
     }
-    for (; u < units; u += stride) body(u / nr, col, acc);
+#pragma unroll 1
+    for (; node < n_nodes; node += step) body(node, col, acc);
   }
   if constexpr (NDOT > 0) {
-    __shared__ Acc sh[256 * NDOT];
-#pragma unroll
-    for (int d = 0; d < NDOT; ++d) sh[d * 256 + threadIdx.x] = acc[d];
-    __syncthreads();
+    // sum the work-items of each case in a fixed tree: bd / nr of them, nr
+    // apart.  Powers of two (the lanes of a case then lie in every wavefront):
+    // across the wavefront, then its four sums; others: halving in LDS.  (One
+    // work-item per output adding its values one after another took 7 us
+    // at one case.)
+    __shared__ Acc sh[kMaxThreads * NDOT];
     const int nsum = NDOT * nr;
-    if (threadIdx.x < nsum) {
-      const int d = threadIdx.x / nr, c = threadIdx.x % nr;
-      Acc s = Acc(0);
-      for (int k = c; k < bd; k += nr) s += sh[d * 256 + k];
-      partials[size_t(threadIdx.x) * kMaxBlocks + blockIdx.x] = s;
+    if ((nr & (nr - 1)) == 0) {
+      const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+      for (int d = 0; d < NDOT; ++d) {
+        for (int off = 32; off >= nr; off >>= 1) acc[d] += __shfl_xor(acc[d], off, 64);
+        if (lane < nr) sh[wave * nsum + d * nr + lane] = acc[d];
+      }
+      __syncthreads();
+      if (int(threadIdx.x) < nsum) {
+        Acc s = Acc(0);
+        for (int w = 0; w < threads / 64; w += 4)
+          s += (sh[w * nsum + threadIdx.x] + sh[(w + 1) * nsum + threadIdx.x]) +
+               (sh[(w + 2) * nsum + threadIdx.x] + sh[(w + 3) * nsum + threadIdx.x]);
+        partials[size_t(threadIdx.x) * kMaxBlocks + blockIdx.x] = s;
+      }
+    } else {
+#pragma unroll
+      for (int d = 0; d < NDOT; ++d) sh[d * threads + threadIdx.x] = acc[d];
+      const int groups = bd / nr, g = int(threadIdx.x) / nr;
+      for (int s = threads / 2; s > 0; s >>= 1) {
+        if (s >= groups) continue;
+        __syncthreads();
+        if (g < s && g + s < groups) {
+#pragma unroll
+          for (int d = 0; d < NDOT; ++d) sh[d * threads + threadIdx.x] += sh[d * threads + threadIdx.x + s * nr];
+        }
+      }
+      __syncthreads();
+      if (int(threadIdx.x) < nsum)
+        partials[size_t(threadIdx.x) * kMaxBlocks + blockIdx.x] = sh[(threadIdx.x / nr) * threads + threadIdx.x % nr];
     }
   }
 }
 
-// Sum the partials of `blocks` workgroups with 256 work-items: output o gets
-// partials b = t, t + 256, t + 512, t + 768 from work-item t (eight outputs'
-// loads in flight at once), then a fixed-order wavefront tree and a sum over
-// the 4 wavefronts (deterministic), and run the epilogue on the totals.
+// Sum the partials of `blocks` workgroups and run the epilogue on the totals.
+// Each of the 16 wavefronts takes the outputs of its number modulo 16, up to
+// two at a time with all their loads in flight together, and adds them in a
+// fixed wavefront tree (deterministic).  (256 work-items taking eight outputs
+// a round waited four rounds of loads at 16 cases and two sums: 8.5 us.)
 template <typename Acc, int NDOT, class Epi>
-__global__ __launch_bounds__(256) void k_nodecase_epi(Epi epi, int nr, int blocks, const Acc* __restrict__ partials,
-                                                      const int* __restrict__ gate) {
-  static_assert(kMaxBlocks == 4 * 256, "four partials per work-item");
+__global__ __launch_bounds__(1024) void k_nodecase_epi(Epi epi, int nr, int blocks, const Acc* __restrict__ partials,
+                                                       const int* __restrict__ gate) {
+  constexpr int PER = kMaxBlocks / 64;  // partials of an output per lane
   if (gate && *gate == 0) return;
   __shared__ double tot[3 * EBE_MAX_RHS];
-  __shared__ double wsum[4][3 * EBE_MAX_RHS];
   const int nsum = NDOT * nr;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Every load reads a written partial (indices clamped to the last output
-  // and workgroup), so all of them can be in flight together; the clamped
-  // duplicates are then weighted by zero.  (A duplicate can only be
-  // non-finite if an entry of the sum itself is, so the sum is unchanged.)
-  for (int o0 = 0; o0 < nsum; o0 += 8) {
-    double v[8][4];
+  for (int o0 = wave; o0 < nsum; o0 += 32) {
+    double s[2] = {0.0, 0.0};
+    Acc v[2][PER];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int b = int(threadIdx.x) + 256 * q;
-        const int o = o0 + j;
-        const double w = double(partials[size_t(o < nsum ? o : nsum - 1) * kMaxBlocks + (b < blocks ? b : blocks - 1)]);
-        v[j][q] = w * ((o < nsum && b < blocks) ? 1.0 : 0.0);
+      for (int q = 0; q < PER; ++q) {
+        const int o = o0 + 16 * j, b = lane + 64 * q;
+        v[j][q] = (o < nsum && b < blocks) ? partials[size_t(o) * kMaxBlocks + b] : Acc(0);
       }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      double s = (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);
+    for (int j = 0; j < 2; ++j) {
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-      if (lane == 0 && o0 + j < nsum) wsum[wave][o0 + j] = s;
+      for (int q = 0; q < PER; q += 4)
+        s[j] += (double(v[j][q]) + double(v[j][q + 1])) + (double(v[j][q + 2]) + double(v[j][q + 3]));
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) s[j] += __shfl_xor(s[j], off, 64);
+      if (lane == 0 && o0 + 16 * j < nsum) tot[o0 + 16 * j] = s[j];
     }
   }
-  __syncthreads();
-  if (int(threadIdx.x) < nsum)
-    tot[threadIdx.x] = (wsum[0][threadIdx.x] + wsum[1][threadIdx.x]) + (wsum[2][threadIdx.x] + wsum[3][threadIdx.x]);
   __syncthreads();
   // per-case scalar steps on wavefront 0, the loop test's maximum and the
   // flags combined across it, then the shared step
@@ -141,17 +172,20 @@ __global__ __launch_bounds__(256) void k_nodecase_epi(Epi epi, int nr, int block
 template <typename Acc, int NDOT, class Body, class Epi>
 hipError_t run_nodecase(Body body, Epi epi, int64_t n_nodes, int nr, SolverState& st, const int* gate,
                         hipStream_t s) {
-  const int bd = block_for(nr);
+  const int most = NDOT > 0 ? kMaxBlocks : kMaxBlocksNoSum;
+  int threads = 256;
+  while (threads < kMaxThreads && n_nodes * nr > int64_t(most) * block_for(threads, nr)) threads *= 2;
+  const int bd = block_for(threads, nr);
   int64_t g = (n_nodes * nr + bd - 1) / bd;
-  if (g > kMaxBlocks) g = kMaxBlocks;
+  if (g > most) g = most;
   if (g < 1) g = 1;
   Acc* partials = reinterpret_cast<Acc*>(st.partials);
-  hipLaunchKernelGGL((k_nodecase<Acc, NDOT, Body>), dim3(unsigned(g)), dim3(256), 0, s, body, n_nodes, nr, partials,
+  hipLaunchKernelGGL((k_nodecase<Acc, NDOT, Body>), dim3(unsigned(g)), dim3(unsigned(threads)), 0, s, body, n_nodes, nr, partials,
                      gate);
   if constexpr (NDOT > 0) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_nodecase_epi<Acc, NDOT, Epi>), dim3(1), dim3(256), 0, s, epi, nr, int(g), partials, gate);
+    hipLaunchKernelGGL((k_nodecase_epi<Acc, NDOT, Epi>), dim3(1), dim3(1024), 0, s, epi, nr, int(g), partials, gate);
   }
   return hipGetLastError();
 }
