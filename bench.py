@@ -57,7 +57,7 @@ def product_bytes(N, Nv, E, n, p):
 
 def source_hash():
     h = hashlib.sha256()
-    for f in ("ebe_kernels.hip", "fan_kernel.h", "pipe_kernel.h", "patch_common.h", "p2_element.h", "patches.cpp", "ebe_internal.h"):
+    for f in ("ebe_kernels.hip", "fan_kernel.h", "ebe_wide.hip", "pipe_kernel.h", "patch_common.h", "p2_element.h", "patches.cpp", "ebe_internal.h"):
         with open(os.path.join(ROOT, "paper_1710_08679_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

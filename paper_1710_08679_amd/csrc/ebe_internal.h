@@ -129,6 +129,22 @@ struct Workspace {
 constexpr int kFanLen = 3;
 constexpr int kFanWords = 6 + 4 * kFanLen;
 constexpr int kFanStride = kFanWords + 2;
+// Wide patches (ebe_wide.hip): runs of consecutive patches for products of at
+// most kWideCases cases, in two sizes (blocks of 2x4x4 and 4x4x4 hexahedra of a
+// Morton-ordered mesh): at most so many elements, nodes and corners.  Rows of
+// kWideStride patch-local ids per fan: the kFanWords nodes, then the number of
+// tetrahedra.
+constexpr int kWideSizes = 2;
+constexpr int kWideElems[kWideSizes] = {192, 384};
+constexpr int kWideNodes[kWideSizes] = {408, 736};
+constexpr int kWideCorners[kWideSizes] = {128, 160};
+constexpr int kWideCases = 4;
+constexpr int kWideStride = 24;
+// the size a product takes: FP32 at three or four cases the smaller (its
+// accumulator leaves room for three workgroups of four wavefronts; 64^3 cube,
+// 4 cases 207 us against 229), the others the larger (FP64 1 case 131 -> 116
+// us, FP64 4 cases 376 -> 335 us, FP32 1 case 87 -> 71 us)
+constexpr int wide_size(int value_bytes, int nr) { return value_bytes == 4 && nr >= 3 ? 0 : 1; }
 constexpr int kSliceRows = 64;  // rows per slice of an assembled operator (AsmOp)
 constexpr int kA2MaxRow = 800;  // longest level-2 row (blocks) whose sums fit 64 KB of LDS
 constexpr int kPatchElems = EBE_PATCH_ELEMS;
@@ -210,6 +226,13 @@ struct ebe_mesh {
   ebe::DBuf fanw;       // uint32 [nfan][kFanStride]
   ebe::DBuf felem;      // int32 [nfan][kFanLen] element, -1: none
   int64_t nfan = 0;
+  // wide patches of each size
+  struct Wide {
+    ebe::PatchLevel pl;   // node tables (corners first) and staging slots; staged in pl[0].stage
+    ebe::DBuf pfan;       // int32 [pl.npatch+1] fan offsets
+    ebe::DBuf pcorner;    // int32 [pl.npatch] corners
+    ebe::DBuf fanl;       // uint16 [nfan][kWideStride] the fans' patch-local ids
+  } wide[ebe::kWideSizes];
   ebe::DBuf gacc;       // kGammaBytes: (x, K x) slots, then the arrival counter; zero between products
   // EBE product form per [level][dtype F64, F32][nrhs]: one of the forms, or
   // EBE_FORM_AUTO (untuned: a fixed default)

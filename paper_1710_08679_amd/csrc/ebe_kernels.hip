@@ -540,6 +540,9 @@ hipError_t ebe_dispatch_p(int order, int form, const ebe_mesh* m, const void* x,
     return launch_asm_p<T, NR>(m, m->k1, fx, x, y, mask_in, bc, add, gate, s, gamma);
   }
   if (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED) {
+    if constexpr (NR <= kWideCases) {
+      if (order == 2 && form == EBE_FORM_PIPELINED) return launch_wide<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma);
+    }
     if (order == 2)
       return launch_fan<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma, form == EBE_FORM_COLOURED);
     return m->fvar[1][sizeof(T) == 8 ? 0 : 1][NR] != 1
@@ -670,7 +673,10 @@ ebe_status ensure_stage(ebe_mesh* m, int nrhs, size_t elem_bytes) {
       set_error("mesh too large for 32-bit staging indices (%lld slots)", (long long)L.nslots);
       return EBE_ERR_ARG;
     }
-    const size_t need = size_t(L.nslots) * 3 * size_t(nrhs) * elem_bytes;
+    int64_t slots = L.nslots;
+    if (l == 0 && nrhs <= kWideCases)
+      slots = std::max(slots, m->wide[wide_size(int(elem_bytes), nrhs)].pl.nslots);
+    const size_t need = size_t(slots) * 3 * size_t(nrhs) * elem_bytes;
     ebe_status st = m->pl[l].stage.alloc(need);
     if (st != EBE_OK) return st;
   }

@@ -265,5 +265,9 @@ hipError_t launch_pipe(const ebe_mesh* m, const void* x, void* y, bool mask_in, 
 template <typename T, int NR>
 hipError_t launch_fan(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add, const int* gate,
                       hipStream_t s, double* gamma, bool colour);
+// the pipelined form's kernel at NR <= kWideCases cases (ebe_wide.hip)
+template <typename T, int NR>
+hipError_t launch_wide(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add, const int* gate,
+                       hipStream_t s, double* gamma);
 
 }  // namespace ebe

@@ -55,6 +55,35 @@ struct LevelTables {
   int max_nodes = 0;
 };
 
+// Staging slots and the shared nodes' lists from a level's patch entries
+// (pnode: plain node ids; count: patches touching each node).  The partial
+// sums of one shared node sit in consecutive slots, nodes in increasing id, a
+// node's partials in patch order.
+void stage_level(int64_t n_nodes, const uint8_t* fix, const std::vector<int32_t>& count, LevelTables& t) {
+  // start[] is cumulative over shared nodes only, so it doubles as the offset list
+  std::vector<int64_t> start(n_nodes + 1, 0);
+  for (int64_t v = 0; v < n_nodes; ++v) start[v + 1] = start[v] + (count[v] > 1 ? count[v] : 0);
+  t.nslots = start[n_nodes];
+  t.pslot.assign(t.pnode.size(), -1);
+  std::vector<int64_t> fill(start.begin(), start.end() - 1);
+  for (size_t i = 0; i < t.pnode.size(); ++i) {
+    const int32_t v = t.pnode[i];
+    if (count[v] > 1) t.pslot[i] = int32_t(fill[v]++);
+  }
+  t.snode.clear();
+  t.soff.assign(1, 0);
+  for (int64_t v = 0; v < n_nodes; ++v)
+    if (count[v] > 1) {
+      t.snode.push_back(int32_t(v) | (int32_t(fix[v]) << kIdxBits));
+      t.soff.push_back(int32_t(start[v + 1]));
+    }
+  // pack node words: id | fix bits | shared flag
+  for (size_t i = 0; i < t.pnode.size(); ++i) {
+    const int32_t v = t.pnode[i];
+    t.pnode[i] = v | (int32_t(fix[v]) << kIdxBits) | (count[v] > 1 ? int32_t(1u << 31) : 0);
+  }
+}
+
 // Entries of one level: nodes_of(e, a) for local slot a < nloc.
 template <class NodeOf>
 void build_level(const std::vector<int32_t>& pelem, int nloc, int64_t n_nodes, const uint8_t* fix,
@@ -80,30 +109,7 @@ void build_level(const std::vector<int32_t>& pelem, int nloc, int64_t n_nodes, c
     t.poff[p + 1] = int32_t(t.pnode.size());
     t.max_nodes = std::max(t.max_nodes, t.poff[p + 1] - base);
   }
-  // Staging slots: the partial sums of one shared node sit in consecutive
-  // slots, nodes in increasing id, a node's partials in patch order.  start[]
-  // is cumulative over shared nodes only, so it doubles as the offset list.
-  std::vector<int64_t> start(n_nodes + 1, 0);
-  for (int64_t v = 0; v < n_nodes; ++v) start[v + 1] = start[v] + (count[v] > 1 ? count[v] : 0);
-  t.nslots = start[n_nodes];
-  t.pslot.assign(t.pnode.size(), -1);
-  std::vector<int64_t> fill(start.begin(), start.end() - 1);
-  for (size_t i = 0; i < t.pnode.size(); ++i) {
-    const int32_t v = t.pnode[i];
-    if (count[v] > 1) t.pslot[i] = int32_t(fill[v]++);
-  }
-  t.snode.clear();
-  t.soff.assign(1, 0);
-  for (int64_t v = 0; v < n_nodes; ++v)
-    if (count[v] > 1) {
-      t.snode.push_back(int32_t(v) | (int32_t(fix[v]) << kIdxBits));
-      t.soff.push_back(int32_t(start[v + 1]));
-    }
-  // pack node words: id | fix bits | shared flag
-  for (size_t i = 0; i < t.pnode.size(); ++i) {
-    const int32_t v = t.pnode[i];
-    t.pnode[i] = v | (int32_t(fix[v]) << kIdxBits) | (count[v] > 1 ? int32_t(1u << 31) : 0);
-  }
+  stage_level(n_nodes, fix, count, t);
 }
 
 // Cut elements, in order, into ranges of at most max_elems elements touching
@@ -311,6 +317,69 @@ void build_fans(const std::vector<int32_t>& pelem, const int32_t* conn10, const 
   });
 }
 
+// Wide patches of a size: consecutive patches of level 0 put together while
+// they have at most its elements, distinct nodes and corners (a single patch is
+// always within them); corners first.
+struct WideTables {
+  LevelTables t;
+  std::vector<int32_t> pfan;     // fan offsets
+  std::vector<int32_t> pcorner;  // corners (the first nodes) of each
+  std::vector<uint16_t> fanl;    // [nfan][kWideStride] patch-local ids
+};
+void build_wide(const std::vector<int32_t>& pelem, const LevelTables& t0, int64_t n_nodes, int64_t n_vertices,
+                const uint8_t* fix, const std::vector<int32_t>& pfan, const std::vector<uint32_t>& fanw, int size,
+                WideTables& w) {
+  const int max_elems = kWideElems[size], max_nodes = kWideNodes[size], max_corners = kWideCorners[size];
+  const int64_t npatch = int64_t(pelem.size()) - 1, nfan = pfan[npatch];
+  std::vector<int32_t> stamp(n_nodes, -1), local(n_nodes, 0), count(n_nodes, 0);
+  w.t.poff.assign(1, 0);
+  w.pfan.assign(1, 0);
+  w.pcorner.clear();
+  w.fanl.assign(size_t(nfan) * kWideStride, 0);
+  auto entries = [&](int64_t p, auto&& f) {
+    for (int32_t i = t0.poff[p]; i < t0.poff[p + 1]; ++i) f(t0.pnode[i] & kIdxMask);
+  };
+  for (int64_t p0 = 0, p1 = 0; p0 < npatch; p0 = p1) {
+    const int32_t id = int32_t(w.pcorner.size());
+    int32_t nn = 0, nc = 0;
+    for (p1 = p0; p1 < npatch; ++p1) {
+      int32_t fresh = 0, corners = 0;
+      entries(p1, [&](int32_t v) {
+        fresh += stamp[v] != id;
+        corners += stamp[v] != id && v < n_vertices;
+      });
+      if (p1 > p0 && (pelem[p1 + 1] - pelem[p0] > max_elems || nn + fresh > max_nodes || nc + corners > max_corners))
+        break;
+      entries(p1, [&](int32_t v) { stamp[v] = id; });
+      nn += fresh;
+      nc += corners;
+    }
+    // the nodes, corners first
+    const size_t o0 = w.t.pnode.size();
+    for (int pass = 0; pass < 2; ++pass)
+      for (int64_t p = p0; p < p1; ++p)
+        entries(p, [&](int32_t v) {
+          if ((v < n_vertices) != (pass == 0) || stamp[v] != id) return;
+          stamp[v] = -1;
+          local[v] = int32_t(w.t.pnode.size() - o0);
+          w.t.pnode.push_back(v);
+          count[v]++;
+        });
+    for (int32_t f = pfan[p0]; f < pfan[p1]; ++f) {
+      const uint32_t* fw = &fanw[size_t(f) * kFanStride];
+      uint16_t* l = &w.fanl[size_t(f) * kWideStride];
+      const int len = int(fw[kFanWords] & 3u);
+      for (int a = 0; a < 6 + 4 * len; ++a) l[a] = uint16_t(local[fw[a] & kPtabIdMask]);
+      l[kFanWords] = uint16_t(len);
+    }
+    w.t.poff.push_back(int32_t(w.t.pnode.size()));
+    w.pfan.push_back(pfan[p1]);
+    w.pcorner.push_back(nc);
+  }
+  for (size_t i = 0; i + 1 < w.t.poff.size(); ++i) w.t.max_nodes = std::max(w.t.max_nodes, w.t.poff[i + 1] - w.t.poff[i]);
+  stage_level(n_nodes, fix, count, w.t);
+}
+
 // Greedy colouring of the patches (in patch order, each takes the smallest
 // colour no patch sharing a node with it has), the patches listed colour by
 // colour, and the node words with bit 31 set where an earlier patch in that
@@ -369,6 +438,21 @@ ebe_status up(DBuf& b, const std::vector<T>& h, hipStream_t s) {
   if (st != EBE_OK) return st;
   if (!h.empty())
     EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
+  return EBE_OK;
+}
+
+ebe_status up_level(PatchLevel& L, const LevelTables& t, int64_t npatch, hipStream_t s) {
+  ebe_status st = EBE_OK;
+  if ((st = up(L.poff, t.poff, s)) != EBE_OK) return st;
+  if ((st = up(L.pnode, t.pnode, s)) != EBE_OK) return st;
+  if ((st = up(L.pslot, t.pslot, s)) != EBE_OK) return st;
+  if ((st = up(L.snode, t.snode, s)) != EBE_OK) return st;
+  if ((st = up(L.soff, t.soff, s)) != EBE_OK) return st;
+  L.npatch = npatch;
+  L.nslots = t.nslots;
+  L.nshared = int64_t(t.snode.size());
+  L.entries = int64_t(t.pnode.size());
+  L.max_nodes = t.max_nodes;
   return EBE_OK;
 }
 
@@ -433,20 +517,21 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
     if ((st = up(m->pfan, pfan, s)) != EBE_OK) return st;
     if ((st = up(m->fanw, fanw, s)) != EBE_OK) return st;
     if ((st = up(m->felem, felem, s)) != EBE_OK) return st;
+    WideTables w[kWideSizes];
+    parallel(kWideSizes, [&](int k) {
+      build_wide(pelem[0], t[0], m->n_nodes, m->n_vertices, fix, pfan, fanw, k, w[k]);
+    });
+    for (int k = 0; k < kWideSizes; ++k) {
+      ebe_mesh::Wide& d = m->wide[k];
+      if ((st = up(d.pfan, w[k].pfan, s)) != EBE_OK) return st;
+      if ((st = up(d.pcorner, w[k].pcorner, s)) != EBE_OK) return st;
+      if ((st = up(d.fanl, w[k].fanl, s)) != EBE_OK) return st;
+      if ((st = up_level(d.pl, w[k].t, int64_t(w[k].pcorner.size()), s)) != EBE_OK) return st;
+    }
   }
   for (int l = 0; l < 2; ++l) {
-    PatchLevel& L = m->pl[l];
-    if ((st = up(L.pelem, pelem[l], s)) != EBE_OK) return st;
-    if ((st = up(L.poff, t[l].poff, s)) != EBE_OK) return st;
-    if ((st = up(L.pnode, t[l].pnode, s)) != EBE_OK) return st;
-    if ((st = up(L.pslot, t[l].pslot, s)) != EBE_OK) return st;
-    if ((st = up(L.snode, t[l].snode, s)) != EBE_OK) return st;
-    if ((st = up(L.soff, t[l].soff, s)) != EBE_OK) return st;
-    L.npatch = int64_t(pelem[l].size()) - 1;
-    L.nslots = t[l].nslots;
-    L.nshared = int64_t(t[l].snode.size());
-    L.entries = int64_t(t[l].pnode.size());
-    L.max_nodes = t[l].max_nodes;
+    if ((st = up(m->pl[l].pelem, pelem[l], s)) != EBE_OK) return st;
+    if ((st = up_level(m->pl[l], t[l], int64_t(pelem[l].size()) - 1, s)) != EBE_OK) return st;
   }
   return EBE_OK;
 }

@@ -12,7 +12,7 @@ import torch
 
 from oracle import adjoint, fem
 from paper_1710_08679_amd import ebe, meshgen
-from tests.helpers import assert_close_bound, kappa_max, oracle_K, parity_mesh
+from tests.helpers import assert_close_bound, kappa_max, oracle_K, parity_mesh, tol_factor
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +78,31 @@ def test_adjoint_gradient_of_short_fans(case, dtype, tol, nrhs):
     ref = adjoint.element_gradient(m.xyz, m.conn, m.poisson, u * free, lam * free)
     g = gm.adjoint_grad(torch.from_numpy(u).cuda(), torch.from_numpy(lam).cuda()).cpu().numpy()
     assert np.max(np.abs(g - ref)) <= tol * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 4])
+@pytest.mark.parametrize("grid", [(1, 1, 1), (9, 5, 7)])
+def test_wide_patches_of_ragged_meshes(gpu_lib, grid, dtype, nrhs):
+    """One patch that fills a corner of a wide one, and wide patches cut at
+    the ends of Morton blocks; y += K x, and K x with an infinite and a NaN
+    entry in x (they reach the nodes of their elements and no others)."""
+    m = parity_mesh(*grid, seed=6, bc=True)
+    gm, K, kap = ebe.Mesh.from_generated(m), oracle_K(m), kappa_max(m)
+    gm.set_form(0, DT[dtype], nrhs, ebe.FORM_PIPELINED)
+    rng = meshgen.rng_for(93, nrhs)
+    x, y0 = (rng.standard_normal((m.n_nodes, 3, nrhs)).astype(dtype) for _ in range(2))
+    xr = x.astype(np.float64)
+    y = torch.from_numpy(y0).cuda()
+    gm.matvec_add(torch.from_numpy(x).cuda(), y)
+    Kx = (K @ xr.reshape(-1, nrhs)).reshape(x.shape)
+    bound = tol_factor(dtype, kap) * (abs(K) @ np.abs(xr).reshape(-1, nrhs)).reshape(x.shape)
+    ref = y0.astype(np.float64) + Kx
+    assert np.all(np.abs(y.cpu().numpy() - ref) <= bound + 2 * np.finfo(dtype).eps * np.abs(ref))
+    x[0, 0, 0], x[m.n_nodes - 1, 2, nrhs - 1] = np.inf, np.nan
+    y = gm.matvec(torch.from_numpy(x).cuda()).cpu().numpy()
+    touched = np.zeros((m.n_nodes, nrhs), dtype=bool)
+    for node, r in ((0, 0), (m.n_nodes - 1, nrhs - 1)):
+        touched[np.unique(m.conn[(m.conn == node).any(axis=1)]), r] = True
+    assert np.all(np.isfinite(y) | touched[:, None, :])
+    assert not np.isfinite(y[0, :, 0]).any() and not np.isfinite(y[m.n_nodes - 1, :, nrhs - 1]).any()
