@@ -57,15 +57,27 @@ EBE_HD T tet_geometry(const T a[3], const T b[3], const T c[3], T G[4][3]) {
   return det * T(1.0 / 6.0);
 }
 
-// The same from the corners.  Edge vectors are formed in FP64 (coordinates
-// are FP64), the rest in T.
+// The same from the corners (written out: a call of the above changes the
+// order of the gather form's instructions).  Edge vectors are formed in FP64
+// (coordinates are FP64), the rest in T.
 template <typename T>
 EBE_HD T tet_geometry(const double4& p0, const double4& p1, const double4& p2,
                                           const double4& p3, T G[4][3]) {
-  const T a[3] = {T(p1.x - p0.x), T(p1.y - p0.y), T(p1.z - p0.z)};
-  const T b[3] = {T(p2.x - p0.x), T(p2.y - p0.y), T(p2.z - p0.z)};
-  const T c[3] = {T(p3.x - p0.x), T(p3.y - p0.y), T(p3.z - p0.z)};
-  return tet_geometry<T>(a, b, c, G);
+  const T a0 = T(p1.x - p0.x), a1 = T(p1.y - p0.y), a2 = T(p1.z - p0.z);
+  const T b0 = T(p2.x - p0.x), b1 = T(p2.y - p0.y), b2 = T(p2.z - p0.z);
+  const T c0 = T(p3.x - p0.x), c1 = T(p3.y - p0.y), c2 = T(p3.z - p0.z);
+  // rows of the inverse Jacobian: (b x c, c x a, a x b) / det
+  const T bc0 = b1 * c2 - b2 * c1, bc1 = b2 * c0 - b0 * c2, bc2 = b0 * c1 - b1 * c0;
+  const T ca0 = c1 * a2 - c2 * a1, ca1 = c2 * a0 - c0 * a2, ca2 = c0 * a1 - c1 * a0;
+  const T ab0 = a1 * b2 - a2 * b1, ab1 = a2 * b0 - a0 * b2, ab2 = a0 * b1 - a1 * b0;
+  const T det = a0 * bc0 + a1 * bc1 + a2 * bc2;
+  const T inv = T(1) / det;
+  G[1][0] = bc0 * inv; G[1][1] = bc1 * inv; G[1][2] = bc2 * inv;
+  G[2][0] = ca0 * inv; G[2][1] = ca1 * inv; G[2][2] = ca2 * inv;
+  G[3][0] = ab0 * inv; G[3][1] = ab1 * inv; G[3][2] = ab2 * inv;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) G[0][d] = -(G[1][d] + G[2][d] + G[3][d]);
+  return det * T(1.0 / 6.0);
 }
 
 // w += engineering strain of the outer product d (x) g
@@ -179,10 +191,8 @@ EBE_HD void p2_apply(const T G[4][3], T cl, T cm, U&& u, Emit&& emit, bool with_
     fma_eng(w[k], ue, G[m]);
     fma_eng(w[m], ue, G[k]);
   }
-  // S'_k from the strain 4 w_k - A (w is overwritten by S'_k).  With the
-  // energy, the strains' sum is kept and S' formed from it at the end (S is
-  // linear in e), so no second sum is live
-  T Ssum[6];
+  // S'_k from the strain 4 w_k - A (w is overwritten by S'_k)
+  T Ssum[6], esum[6];
   T en = T(0);
   const T cm2 = cm + cm;
 #pragma unroll
@@ -198,20 +208,18 @@ EBE_HD void p2_apply(const T G[4][3], T cl, T cm, U&& u, Emit&& emit, bool with_
     w[k][4] = cm * e[4];
     w[k][5] = cm * e[5];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      const T v = with_energy ? e[c] : w[k][c];
-      Ssum[c] = (k == 0) ? v : Ssum[c] + v;
-      if (with_energy) en += w[k][c] * e[c];
+    for (int c = 0; c < 6; ++c) Ssum[c] = (k == 0) ? w[k][c] : Ssum[c] + w[k][c];
+    if (with_energy) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        en += w[k][c] * e[c];
+        esum[c] = (k == 0) ? e[c] : esum[c] + e[c];
+      }
     }
   }
   if (with_energy) {
-    const T clt = cl * ((Ssum[0] + Ssum[1]) + Ssum[2]);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      const T ec = Ssum[c];
-      Ssum[c] = c < 3 ? cm2 * ec + clt : cm * ec;
-      en += Ssum[c] * ec;
-    }
+    for (int c = 0; c < 6; ++c) en += Ssum[c] * esum[c];
     energy = en;
   }
   // corners: f_i = (4 S'_i - S') G_i
