@@ -196,6 +196,20 @@ constexpr int kPtabLocalShift = 25;
 constexpr uint32_t kPtabIdMask = (1u << kPtabLocalShift) - 1;
 static_assert(kPatchNodes <= 128 && kLinPatchCorners <= 128, "patch-local ids must fit 7 bits");
 
+constexpr int kXcds = 8;  // dies of the GPU, each with an L2 of its own
+
+// Chains of the pipelined quadratic form: kChain consecutive patches in an
+// order in which neighbours share many nodes.  The workgroup that works through
+// a chain keeps the accumulator rows that the next patch shares, so a face
+// between two patches costs no partial sums of its own.  Of an XCD's cnt
+// patches the first fan_chained(cnt) are in chains and the others single, which
+// evens out the workgroups' shares: whole rounds of 64 or 96 workgroups an XCD
+// (two or three per CU, FP64 and FP32 at 16 cases).
+constexpr int kChain = 4;
+constexpr int64_t kChainRound = 192 * kChain;
+constexpr int32_t kNoEntry = kIdxMask;
+constexpr int64_t fan_chained(int64_t cnt) { return cnt / kChainRound * kChainRound; }
+
 }  // namespace ebe
 
 struct ebe_mesh {
@@ -226,6 +240,14 @@ struct ebe_mesh {
   ebe::DBuf fanw;       // uint32 [nfan][kFanStride]
   ebe::DBuf felem;      // int32 [nfan][kFanLen] element, -1: none
   int64_t nfan = 0;
+  // pipelined form: the patches in the order it takes them, and the nodes each
+  // one finishes (see fan_chained); staged in pl[0].stage
+  ebe::PatchLevel chain;
+  ebe::DBuf cseq;       // int32 [npatch] patch at a place of the order
+  ebe::DBuf cslot;      // uint8 [chain.entries] accumulator row of a finished node
+  // coloured form: by patch, pl[0].cword at each node's accumulator row, kNoEntry in between
+  ebe::DBuf croff;      // int32 [npatch+1]
+  ebe::DBuf crow;       // int32
   // wide patches of each size
   struct Wide {
     ebe::PatchLevel pl;   // node tables (corners first) and staging slots; staged in pl[0].stage

@@ -10,16 +10,20 @@
 // of the spoke nodes two tetrahedra share are summed in FP64 registers, as
 // they were in the FP64 accumulator.
 //
-// A persistent workgroup works through a sequence of patches (those of its
-// XCD's contiguous range, in steps of the number of workgroups on that XCD)
-// and keeps the next patch's metadata in flight while it computes the current
-// one.  Per patch:
+// A persistent workgroup works through a sequence of chains of patches (those
+// of its XCD's contiguous range, in steps of the number of workgroups on that
+// XCD) and keeps the next patch's metadata in flight while it computes the
+// current one.  Within a chain the accumulator rows that the next patch shares
+// stay in F, so they are written once, when their last patch of the chain ends:
+// on a mesh of 2x2x2-hexahedron patches 1.13 rows a node are staged and added
+// instead of 1.53 (64^3 cube: FP32 16 cases 638 -> 595 us, FP64 16 cases 1200 ->
+// 1104 us, FP32 8 cases 376 -> 357 us).  Per patch:
 //   A. commit the prefetched node words, staging slots and fan words to LDS
 //      (fan words as byte offsets of the node rows in x and in the FP64
 //      accumulator F, so the element phase adds only its case offset);
 //   B. issue the next patch's loads;
 //   C. element phase: one work-item per (fan, case);
-//   D. write back, zeroing F behind it: exclusive nodes straight into y,
+//   D. write back the finished nodes, zeroing F behind it: exclusive nodes straight into y,
 //      shared nodes as partial sums into their staging slots (a node-centric
 //      pass adds them after).
 //
@@ -46,21 +50,37 @@ constexpr int fan_rim(int i) { return 9 + 4 * i; }                 // edge betwe
 // still fit in a CU's LDS.  Patches of more fans take several rounds.
 constexpr int kFanCap = 20;
 
-// one work-item per (fan, case) of a full patch of full fans
+// Whether a work-item takes one tetrahedron of a fan instead of the whole fan:
+// where the 16 fans of a patch would leave many lanes of their wavefronts idle
+// (16 n work-items on ceil(n / 4) wavefronts, two of which fit a SIMD in FP64;
+// 48 n tetrahedra fill theirs, and their 160 registers leave room for three).
+// Fans / tetrahedra, FP64, 64x64x40 lattice: 5 cases 367 / 343 us, 9 631 / 536,
+// 10 593 / 557, 11 720 / 649, 12 633 / 639 (but 35.1 / 32.6 at 15x17x26), 13 761
+// / 724; 6 360 / 381, 8 374 / 473, 16 666 / 795.  FP32: 9 495 / 448, 10 441 / 421;
+// 5 234 / 262, 8 223 / 260, 12 341 / 405, 16 370 / 418.
+template <typename T>
+constexpr bool fan_singles(int nr) {
+  return nr == 9 || nr == 10 || (sizeof(T) == 8 && (nr == 5 || (nr >= 11 && nr <= 13)));
+}
+// one work-item per (fan or tetrahedron, case) of a full patch of full fans
+template <typename T>
 constexpr int fan_threads(int nr) {
+  if (fan_singles<T>(nr)) return threads_for(nr, 2, int(sizeof(T)), false);
   const int g = 64 / nr;  // fans per wavefront
-  const int want = ((kPatchElems / kFanLen + g - 1) / g * g * nr + 63) / 64 * 64;
+  const int fans = kPatchElems / kFanLen;
+  // 4, 8, 12, 16 cases fill whole wavefronts in any case
+  const int want = nr % 4 == 0 ? fans * nr : ((fans + g - 1) / g * g * nr + 63) / 64 * 64;
   return want > 256 ? 256 : want;
 }
-constexpr int fan_lds_bytes(int nr) { return kPatchNodes * 3 * nr * 8 + kFanCap * kFanStride * 8 + 8 * kPatchNodes + 8 * nr + 16; }
+constexpr int fan_lds_bytes(int nr) { return kPatchNodes * 3 * nr * 8 + kFanCap * kFanStride * 8 + 9 * kPatchNodes + 8 * nr + 16; }
 // Wavefronts per SIMD that the LDS of a workgroup leaves room for, at most
 // three in FP32 (168 registers: three tetrahedra's shared sums stay in
 // registers) and two in FP64 (256).
 template <typename T>
 constexpr int fan_waves_per_simd(int nr) {
   const int wg = 163840 / ((fan_lds_bytes(nr) + 1279) / 1280 * 1280);
-  const int w = (wg * (fan_threads(nr) / 64) + 3) / 4;
-  const int most = sizeof(T) == 8 ? 2 : 3;
+  const int w = (wg * (fan_threads<T>(nr) / 64) + 3) / 4;
+  const int most = sizeof(T) == 8 ? 2 : (fan_singles<T>(nr) ? 4 : 3);
   return w > most ? most : (w < 1 ? 1 : w);
 }
 
@@ -80,18 +100,20 @@ __device__ __forceinline__ double row_value(double v) {
 // with add), as the sum of each tetrahedron's forces times its nodal values,
 // which are still at hand (from strains and stresses it took more
 // instructions, and registers that made the FP64 kernel spill).  MASK: zero the fixed DOFs of x while reading it.  COLOUR:
-// the coloured form; plist then lists this launch's patches (one colour).
+// the coloured form.  plist lists this launch's patches: all of them
+// in chain order, the node entries being by place in it, or one colour, the
+// entries being by patch.
 template <typename T, int NR, bool MASK, bool GAMMA, bool COLOUR>
-__global__ __launch_bounds__(fan_threads(NR)) __attribute__((amdgpu_waves_per_eu(fan_waves_per_simd<T>(NR)))) void
+__global__ __launch_bounds__(fan_threads<T>(NR)) __attribute__((amdgpu_waves_per_eu(fan_waves_per_simd<T>(NR)))) void
 k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const int32_t* __restrict__ pfan,
           const int32_t* __restrict__ poff, const int32_t* __restrict__ pnode, const int32_t* __restrict__ pslot,
-          const int32_t* __restrict__ plist, const T* __restrict__ x, T* __restrict__ y, T* __restrict__ stage,
+          const uint8_t* __restrict__ prow, const int32_t* __restrict__ plist, const T* __restrict__ x, T* __restrict__ y, T* __restrict__ stage,
           int stream, int npatch, int bc, int add, double* __restrict__ gamma, double* __restrict__ gslot,
           unsigned* __restrict__ gcount, const int* __restrict__ gate) {
   constexpr int W = 3 * NR;                         // values of a node row
   constexpr uint32_t RB = uint32_t(W * sizeof(T));  // bytes of a node row in x and y
   constexpr uint32_t FB = uint32_t(W * 8);          // bytes of a node row in F
-  constexpr int TPB = fan_threads(NR);
+  constexpr int TPB = fan_threads<T>(NR);
   constexpr int MAXN = kPatchNodes;
   constexpr int KW = (MAXN + TPB - 1) / TPB;              // node entries per work-item
   constexpr int NT = kFanCap * kFanStride;                // fan words in LDS
@@ -102,6 +124,7 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
   constexpr int KIT = (MAXN + EPK - 1) / EPK;
   constexpr int G = 64 / NR;                              // fans per wavefront
   constexpr int GV = 16 / int(sizeof(T));
+  constexpr bool kTouch = !COLOUR && (sizeof(T) == 8 || fan_singles<T>(NR));
   constexpr bool kRowLane = NR == 16 && sizeof(T) == 8;
   using V = VecT<T, VEC>;
   using GR = VecT<T, GV>;
@@ -110,33 +133,45 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
   __shared__ __align__(16) uint32_t ftab[kFanCap][kFanStride];  // F-row byte offsets
   __shared__ int32_t words[MAXN];
   __shared__ int32_t slots[COLOUR ? 1 : MAXN];
+  __shared__ uint8_t rows[COLOUR ? 1 : MAXN];  // the entries' rows of F (coloured: entry i has row i)
   __shared__ double gsum[NR];
   if (gate && *gate == 0) return;
   const int tid = threadIdx.x;
-  // this workgroup's patches: XCD x owns [start, stop); its g-th workgroup
-  // takes start + g, start + g + wx, ...
+  // this workgroup's patches: XCD x owns [start, stop), in units of one chain
+  // and, after those, of one patch; its g-th workgroup takes units g, g + wx, ...
   const int Gd = gridDim.x, xcd = blockIdx.x % kXcds;
   const int wx = (Gd - xcd + kXcds - 1) / kXcds;  // workgroups on this XCD
   const int q = npatch / kXcds, rr = npatch % kXcds;
   const int start = xcd * q + (xcd < rr ? xcd : rr), stop = start + q + (xcd < rr ? 1 : 0);
-  int p = start + int(blockIdx.x) / kXcds;
+  const int nchain = COLOUR ? 0 : int(fan_chained(stop - start)) / kChain;
+  int unit = int(blockIdx.x) / kXcds;
+  auto unit_place = [&](int u) { return start + u + (kChain - 1) * min(u, nchain); };
+  auto step = [&](int pp) {  // the place after pp; advances to the next unit at the end of one
+    if (unit < nchain && (pp + 1 - start) % kChain != 0) return pp + 1;
+    unit += wx;
+    return unit_place(unit);
+  };
+  int p = unit_place(unit);
   if (GAMMA && tid < NR) gsum[tid] = 0.0;
   // F starts at zero; every write-back zeroes what it read, so it stays zero between patches
   for (int i = tid; i < MAXN * W; i += TPB) F[i] = 0.0;
   // prefetched state of the next patch
   int f0 = 0, nf = 0, o0 = 0, nn = 0;
-  int pw[KW], ps[KW];
+  int pw[KW], ps[KW], pr[KW];
   uint32_t pt[KF];
+  uint32_t touched = 0;
   auto fetch = [&](int pp) {
-    const int id = COLOUR ? plist[pp] : pp;
+    const bool chained = unit < nchain;  // (a single patch takes its place in the order, its entries their own rows)
+    const int id = COLOUR || chained ? plist[pp] : pp, en = COLOUR ? id : pp;
     f0 = pfan[id];
     nf = pfan[id + 1] - f0;
-    o0 = poff[id];
-    nn = poff[id + 1] - o0;
+    o0 = poff[en];
+    nn = poff[en + 1] - o0;
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
       const int i = tid + k * TPB;
       pw[k] = i < nn ? pnode[o0 + i] : 0;
+      if constexpr (!COLOUR) pr[k] = chained && i < nn ? prow[o0 + i] : i;
       if constexpr (!COLOUR) ps[k] = i < nn ? pslot[o0 + i] : 0;
     }
 #pragma unroll
@@ -144,6 +179,12 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
       const int i = tid + k * TPB;
       pt[k] = (i < NT && i < nf * kFanStride) ? fanw[size_t(f0) * kFanStride + i] : 0u;
     }
+    // one word of each 128-byte line of the patch's geometry, so that the
+    // element phase finds it in L2 (FP64 2-3% faster, FP32 by fans 0-1% slower)
+    if constexpr (kTouch)
+      if (tid * 128 < nf * kFanLen * 16 * int(sizeof(T)))
+        touched = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(gfan) +
+                                                     size_t(f0) * (kFanLen * 16 * sizeof(T)) + tid * 128);
   };
   auto put_word = [&](int i, uint32_t w) {  // word i of the LDS tables
     const int f = i / kFanStride, a = i - f * kFanStride;
@@ -157,14 +198,17 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
   constexpr bool kLaneCase = (64 % NR) == 0 && (TPB % NR) == 0;
   double en_acc = 0.0;
 #pragma unroll 1
-  for (; p < stop; p += wx) {
+  while (p < stop) {
     // A. commit this patch
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
       const int i = tid + k * TPB;
       if (i < nn) {
         words[i] = pw[k];
-        if constexpr (!COLOUR) slots[i] = ps[k];
+        if constexpr (!COLOUR) {
+          slots[i] = ps[k];
+          rows[i] = uint8_t(pr[k]);
+        }
       }
     }
 #pragma unroll
@@ -175,8 +219,8 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
     const int cf0 = f0, cnf = nf, cnn = nn;
     __syncthreads();
     // B. the next patch's metadata
-    const int pn = p + wx;
-    if (pn < stop) fetch(pn);
+    p = step(p);
+    if (p < stop) fetch(p);
     const char* xb = reinterpret_cast<const char*>(x);
     char* fbase = reinterpret_cast<char*>(F);
     // C. element phase
@@ -189,11 +233,88 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
         __syncthreads();
       }
       const int cf = min(cnf - c0, kFanCap);
-      const int K = (cf + G - 1) / G;  // a wavefront's fans lie K apart (neighbouring fans share nodes)
+      if constexpr (fan_singles<T>(NR)) {  // one work-item per (tetrahedron, case)
+        const int ce = cf * kFanLen;
+        const int K = (ce + G - 1) / G, GP = (ce + K - 1) / K;
 #pragma unroll 1
-      for (int w = tid; w < K * G * NR; w += TPB) {
+        for (int w = tid; w < K * GP * NR; w += TPB) {
+          const int j = w / NR, r = w - j * NR;
+          const int e = (j % GP) * K + j / GP;
+          const int f = e / kFanLen, i = e - f * kFanLen;
+          if (e >= ce) continue;
+          const uint32_t rx = uint32_t(r) * uint32_t(sizeof(T)), rf = uint32_t(r) * 8u;
+          const uint32_t* xt = xtab[f];
+          const uint32_t* ft = ftab[f];
+          const uint32_t flags0 = xt[kFanWords], flags1 = MASK ? xt[kFanWords + 1] : 0u;
+          if (i >= int(flags0 & 3u)) continue;
+          // the ten words by pairs: p, q; pq; words 2 + 4 i .. (spoke i, after pq
+          // where i = 0); words 6 + 4 i .. (spoke i + 1 and the rim)
+          auto offsets = [&](const uint32_t* t, uint32_t r0, uint32_t o[10]) {
+            const uint2* q = reinterpret_cast<const uint2*>(t);
+            const uint2 pq = q[0], a0 = q[1 + 2 * i], a1 = q[2 + 2 * i], b0 = q[3 + 2 * i], b1 = q[4 + 2 * i];
+            const bool z = i == 0;
+            o[0] = pq.x + r0;
+            o[1] = pq.y + r0;
+            o[2] = (z ? a0.y : a0.x) + r0;
+            o[3] = b0.x + r0;
+            o[4] = t[2] + r0;
+            o[5] = (z ? a1.y : a1.x) + r0;
+            o[6] = (z ? a1.x : a0.y) + r0;
+            o[7] = b0.y + r0;
+            o[8] = b1.x + r0;
+            o[9] = b1.y + r0;
+          };
+          uint32_t xo[10], fo[10];
+          offsets(xt, rx, xo);
+          offsets(ft, rf, fo);
+          T Gm[4][3], cl = T(0), cm = T(0);
+          const T* row = gfan + ((size_t(cf0) + c0 + f) * kFanLen + i) * 16;
+#pragma unroll
+          for (int v = 0; v < 16 / GV; ++v) {
+            const GR gv = *reinterpret_cast<const GR*>(row + v * GV);
+#pragma unroll
+            for (int t = 0; t < GV; ++t) {
+              const int k = (v * GV + t) / 4, d = (v * GV + t) % 4;
+              if (d < 3) Gm[k][d] = gv.v[t];
+              else if (k == 0) cl = gv.v[t];
+              else if (k == 1) cm = gv.v[t];
+            }
+          }
+          auto u = [&](int a, int c) -> T {
+            const T v = *reinterpret_cast<const T*>(xb + size_t(xo[a]) + size_t(c) * NR * sizeof(T));
+            if constexpr (MASK) {
+              const int wa = a == 0 ? 0 : a == 1 ? 1 : a == 4 ? 2 : a == 2 ? (i == 0 ? 3 : 2 + 4 * i)
+                           : a == 6 ? (i == 0 ? 4 : 3 + 4 * i) : a == 5 ? (i == 0 ? 5 : 4 + 4 * i)
+                           : a == 3 ? 6 + 4 * i : a == 9 ? 9 + 4 * i : a + 4 * i;  // (7, 8)
+              const uint32_t bit = wa < 10 ? flags0 >> (2 + 3 * wa + c) : flags1 >> (3 * (wa - 10) + c);
+              return (bit & 1u) ? T(0) : v;
+            } else {
+              return v;
+            }
+          };
+          T en = T(0);
+          auto emit = [&](int a, const T fv[3]) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              if constexpr (GAMMA) en += fv[c] * u(a, c);
+              atomicAdd(reinterpret_cast<double*>(fbase + fo[a]) + c * NR, double(fv[c]));
+            }
+          };
+          T unused = T(0);
+          p2_apply<T>(Gm, cl, cm, u, emit, false, unused);
+          if constexpr (GAMMA) {
+            if constexpr (kLaneCase) en_acc += double(en);
+            else atomicAdd(&gsum[r], double(en));
+          }
+        }
+        continue;
+      }
+      // a wavefront's fans lie K apart (neighbouring fans share nodes)
+      const int K = (cf + G - 1) / G, GP = NR % 4 == 0 ? (cf + K - 1) / K : G;
+#pragma unroll 1
+      for (int w = tid; w < K * GP * NR; w += TPB) {
         const int j = w / NR, r = w - j * NR;
-        const int f = (j % G) * K + j / G;
+        const int f = (j % GP) * K + j / GP;
         if (f >= cf) continue;
         const uint32_t rx = uint32_t(r) * uint32_t(sizeof(T)), rf = uint32_t(r) * 8u;
         const uint32_t* xt = xtab[f];
@@ -314,6 +435,7 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
     // the next patch's metadata has arrived before this patch's write-back
     // stores are issued, so the next commit waits for no store
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    if constexpr (kTouch) asm volatile("" ::"v"(touched));
     __syncthreads();
     // D. write back, zeroing F behind it.  Coloured form at 8 or more cases
     // (at 4, FP64, it measured 15% slower): the rows that are read, added to
@@ -336,9 +458,9 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
     for (int k = 0; k < (kReadFirst ? KIT : 0); ++k) {
       const int ent = sent + k * EPK;
       if (ent < cnn) {
-        const int32_t wd = words[ent];
+        const int32_t wd = words[ent];  
         const bool fixed = bc && ((wd >> (kIdxBits + sc)) & 1);
-        if (((!GAMMA && add) || wd < 0) && !fixed) old[k] = yv[uint32_t(wd & kIdxMask) * uint32_t(NV) + uint32_t(sv)];
+        if (((!GAMMA && add && wd != kNoEntry) || wd < 0) && !fixed) old[k] = yv[uint32_t(wd & kIdxMask) * uint32_t(NV) + uint32_t(sv)];
       }
     }
 #pragma unroll
@@ -346,11 +468,13 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
       const int ent = sent + k * EPK;
       if (ent < cnn) {
         const int32_t wd = words[ent];
+        if (COLOUR && wd == kNoEntry) continue;
+        double* const fr = F + (COLOUR ? ent : int(rows[ent])) * W + sq;
         V v;
 #pragma unroll
         for (int t = 0; t < VEC; ++t) {
-          v.v[t] = T(F[ent * W + sq + t]);
-          F[ent * W + sq + t] = 0.0;
+          v.v[t] = T(fr[t]);
+          fr[t] = 0.0;
         }
         const bool fixed = bc && ((wd >> (kIdxBits + sc)) & 1);
         if (!COLOUR && wd < 0) {  // shared node: partial sum to its staging slot
@@ -397,7 +521,7 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
 template <typename T, int NR, bool MASK, bool GAMMA, bool COLOUR>
 hipError_t launch_fan_k(const ebe_mesh* m, const int32_t* plist, int64_t npatch, const void* x, void* y, bool stream,
                         bool bc, bool add, const int* gate, hipStream_t s, double* gamma) {
-  constexpr int TPB = fan_threads(NR);
+  constexpr int TPB = fan_threads<T>(NR);
   static const int per_cu = [] {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_ebe_fan<T, NR, MASK, GAMMA, COLOUR>, TPB, 0) !=
@@ -411,11 +535,12 @@ hipError_t launch_fan_k(const ebe_mesh* m, const int32_t* plist, int64_t npatch,
     cus = 256;
   const int64_t grid = std::min<int64_t>(npatch, int64_t(per_cu) * cus);
   if (grid < 1) return hipSuccess;
-  const PatchLevel& L = m->pl[0];
+  const PatchLevel& L = m->chain;
   hipLaunchKernelGGL((k_ebe_fan<T, NR, MASK, GAMMA, COLOUR>), dim3(unsigned(grid)), dim3(TPB), 0, s,
                      m->gfan[sizeof(T) == 8 ? 0 : 1].as<T>(), m->fanw.as<uint32_t>(), m->pfan.as<int32_t>(),
-                     L.poff.as<int32_t>(), COLOUR ? L.cword.as<int32_t>() : L.pnode.as<int32_t>(),
-                     L.pslot.as<int32_t>(), plist, static_cast<const T*>(x), static_cast<T*>(y), L.stage.as<T>(),
+                     (COLOUR ? m->croff : L.poff).as<int32_t>(), (COLOUR ? m->crow : L.pnode).as<int32_t>(),
+                     L.pslot.as<int32_t>(), m->cslot.as<uint8_t>(), plist,
+                     static_cast<const T*>(x), static_cast<T*>(y), m->pl[0].stage.as<T>(),
                      int(stream), int(npatch), int(bc), int(add), gamma, m->gacc.as<double>(),
                      reinterpret_cast<unsigned*>(m->gacc.as<char>() + kGammaBytes - 64), gate);
   return hipGetLastError();
@@ -437,8 +562,8 @@ hipError_t launch_fan_c(const ebe_mesh* m, const int32_t* plist, int64_t npatch,
 template <typename T, int NR>
 hipError_t launch_fan(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add, const int* gate,
                       hipStream_t s, double* gamma, bool colour) {
-  const PatchLevel& L = m->pl[0];
   if (colour) {
+    const PatchLevel& L = m->pl[0];
     const int32_t* cp = L.cperm.as<int32_t>();
     for (size_t c = 0; c + 1 < L.coff.size(); ++c) {
       const hipError_t e = launch_fan_c<T, NR, true>(m, cp + L.coff[c], L.coff[c + 1] - L.coff[c], x, y, false,
@@ -447,16 +572,21 @@ hipError_t launch_fan(const ebe_mesh* m, const void* x, void* y, bool mask_in, b
     }
     return hipSuccess;
   }
-  // stream the staged partials past the caches when they cannot stay in the
-  // last-level cache until the shared-node pass reads them back
-  const bool st = int64_t(L.nslots) * 3 * NR * int64_t(sizeof(T)) > kStreamStageBytes;
-  hipError_t e = launch_fan_c<T, NR, false>(m, nullptr, L.npatch, x, y, st, mask_in, bc, add, gate, s, gamma);
-  if (e != hipSuccess || L.nshared == 0) return e;
-  const int64_t work = L.nshared * (3 * NR / reduce_width<T, NR>());
-  hipLaunchKernelGGL((k_reduce_shared<T, NR>), dim3(unsigned((work + 255) / 256)), dim3(256), 0, s,
-                     L.snode.as<int32_t>(), L.soff.as<int32_t>(), L.stage.as<T>(), int(st), static_cast<T*>(y),
-                     int32_t(L.nshared), int(bc), int(add), gate);
-  return hipGetLastError();
+  if constexpr (NR > kWideCases) {
+    // stream the staged partials past the caches when they cannot stay in the
+    // last-level cache until the shared-node pass reads them back
+    const PatchLevel& L = m->chain;
+    const bool st = int64_t(L.nslots) * 3 * NR * int64_t(sizeof(T)) > kStreamStageBytes;
+    hipError_t e = launch_fan_c<T, NR, false>(m, m->cseq.as<int32_t>(), L.npatch, x, y, st, mask_in, bc, add, gate, s, gamma);
+    if (e != hipSuccess || L.nshared == 0) return e;
+    const int64_t work = L.nshared * (3 * NR / reduce_width<T, NR>());
+    hipLaunchKernelGGL((k_reduce_shared<T, NR>), dim3(unsigned((work + 255) / 256)), dim3(256), 0, s,
+                       L.snode.as<int32_t>(), L.soff.as<int32_t>(), m->pl[0].stage.as<T>(), int(st), static_cast<T*>(y),
+                       int32_t(L.nshared), int(bc), int(add), gate);
+    return hipGetLastError();
+  } else {
+    return hipErrorInvalidValue;  // the wide patches' kernel takes these
+  }
 }
 
 }  // namespace ebe

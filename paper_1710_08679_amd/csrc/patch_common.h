@@ -115,7 +115,6 @@ constexpr int patch_waves_per_simd(int nr, int order, bool stage, bool curved = 
 // L2.  Give XCD x the contiguous patch range [start_x, start_x + count_x), so
 // that neighbouring patches, which share about half their nodes, read those
 // nodes through the same L2.  A bijection on [0, npatch).
-constexpr int kXcds = 8;
 __device__ __forceinline__ int xcd_patch(int b, int npatch) {
   const int x = b % kXcds, i = b / kXcds;
   const int q = npatch / kXcds, rr = npatch % kXcds;

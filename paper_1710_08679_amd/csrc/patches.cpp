@@ -317,6 +317,124 @@ void build_fans(const std::vector<int32_t>& pelem, const int32_t* conn10, const 
   });
 }
 
+// Chains of patches (see fan_chained): the order of the patches, each one's
+// finished nodes with their accumulator rows, and the rows of all patch nodes
+// for the coloured form; the rows replace the patch-local ids in the fan words.
+struct ChainTables {
+  LevelTables t;               // by place in the order
+  std::vector<int32_t> seq;    // [npatch] patch at each place
+  std::vector<uint8_t> slot;   // [entries of t] accumulator row
+  std::vector<int32_t> croff, crow;  // coloured form: by patch, cword by accumulator row
+};
+void build_chains(const LevelTables& t0, int64_t n_nodes, const uint8_t* fix, const std::vector<int32_t>& pfan,
+                  const std::vector<int32_t>& cword, std::vector<uint32_t>& fanw, ChainTables& c) {
+  const int64_t npatch = int64_t(t0.poff.size()) - 1;
+  c.seq.resize(npatch);
+  std::vector<uint8_t> rows(t0.pnode.size());  // accumulator rows of the patches' nodes
+  struct Part {
+    std::vector<int32_t> pnode, len;
+    std::vector<uint8_t> slot;
+  } part[kXcds];
+  auto first = [&](int x) { return npatch / kXcds * x + std::min<int64_t>(x, npatch % kXcds); };
+  auto range = [&](int x) {
+    Part& out = part[x];
+    const int64_t start = first(x), stop = first(x + 1), chained = start + fan_chained(stop - start);
+    std::vector<int32_t> held, row;  // place whose patch finds the node in the accumulator already, and its row there
+    if (chained > start) {
+      held.assign(n_nodes, -1);
+      row.resize(n_nodes);
+    }
+    std::vector<int32_t> stamp(chained > start ? n_nodes : 0, -1);
+    auto nodes = [&](int64_t p, auto&& f) {
+      for (int32_t i = t0.poff[p]; i < t0.poff[p + 1]; ++i) f(i, t0.pnode[i] & kIdxMask);
+    };
+    int32_t mark = 0;
+    for (int64_t a = start; a < stop;) {
+      const int n = a < chained ? kChain : 1;
+      // the order with the most shared nodes between neighbours (the first of equal ones)
+      int order[kChain] = {0, 1, 2, 3}, best[kChain] = {0, 1, 2, 3}, most = -1;
+      int common[kChain][kChain] = {};
+      for (int i = 0; i + 1 < n; ++i) {
+        ++mark;
+        nodes(a + i, [&](int32_t, int32_t v) { stamp[v] = mark; });
+        for (int j = i + 1; j < n; ++j)
+          nodes(a + j, [&](int32_t, int32_t v) { common[i][j] += stamp[v] == mark; });
+        for (int j = i + 1; j < n; ++j) common[j][i] = common[i][j];
+      }
+      if (n > 1) do {
+          int sum = 0;
+          for (int i = 0; i + 1 < n; ++i) sum += common[order[i]][order[i + 1]];
+          if (sum > most) {
+            most = sum;
+            std::copy(order, order + n, best);
+          }
+        } while (std::next_permutation(order, order + n));
+      for (int k = 0; k < n; ++k) {
+        const int64_t p = a + best[k], place = a + k;
+        c.seq[place] = int32_t(p);
+        bool taken[kPatchNodes] = {};
+        if (k > 0)
+          nodes(p, [&](int32_t, int32_t v) {
+            if (held[v] == place) taken[row[v]] = true;
+          });
+        int free = 0;
+        nodes(p, [&](int32_t i, int32_t v) {
+          if (k > 0 && held[v] == place) {
+            rows[i] = uint8_t(row[v]);
+          } else {
+            while (taken[free]) ++free;
+            rows[i] = uint8_t(free++);
+          }
+        });
+        const bool more = k + 1 < n;
+        ++mark;
+        if (more) nodes(a + best[k + 1], [&](int32_t, int32_t v) { stamp[v] = mark; });
+        const size_t before = out.pnode.size();
+        nodes(p, [&](int32_t i, int32_t v) {
+          if (more && stamp[v] == mark) {
+            held[v] = int32_t(place) + 1;
+            row[v] = rows[i];
+          } else {
+            out.pnode.push_back(v);
+            out.slot.push_back(rows[i]);
+          }
+        });
+        out.len.push_back(int32_t(out.pnode.size() - before));
+        for (int32_t f = pfan[p]; f < pfan[p + 1]; ++f)
+          for (int i = 0; i < kFanWords; ++i) {
+            uint32_t& w = fanw[size_t(f) * kFanStride + i];
+            w = (w & kPtabIdMask) | uint32_t(rows[t0.poff[p] + int32_t(w >> kPtabLocalShift)]) << kPtabLocalShift;
+          }
+      }
+      a += n;
+    }
+  };
+  if (npatch < 2048)
+    for (int x = 0; x < kXcds; ++x) range(x);
+  else
+    parallel(kXcds, range);
+  std::vector<int32_t> count(n_nodes, 0);
+  c.t.poff.assign(1, 0);
+  for (const Part& q : part) {
+    for (int32_t n : q.len) c.t.poff.push_back(c.t.poff.back() + n);
+    for (int32_t v : q.pnode) ++count[v];
+    c.t.pnode.insert(c.t.pnode.end(), q.pnode.begin(), q.pnode.end());
+    c.slot.insert(c.slot.end(), q.slot.begin(), q.slot.end());
+  }
+  c.t.max_nodes = t0.max_nodes;
+  stage_level(n_nodes, fix, count, c.t);
+  c.croff.assign(1, 0);
+  c.crow.reserve(cword.size());
+  for (int64_t p = 0; p < npatch; ++p) {
+    const size_t r0 = c.crow.size();
+    for (int32_t i = t0.poff[p]; i < t0.poff[p + 1]; ++i) {
+      if (r0 + rows[i] >= c.crow.size()) c.crow.resize(r0 + rows[i] + 1, kNoEntry);
+      c.crow[r0 + rows[i]] = cword[i];
+    }
+    c.croff.push_back(int32_t(c.crow.size()));
+  }
+}
+
 // Wide patches of a size: consecutive patches of level 0 put together while
 // they have at most its elements, distinct nodes and corners (a single patch is
 // always within them); corners first.
@@ -479,12 +597,10 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
   if ((st = up(m->lconn1, lconn1, s)) != EBE_OK) return st;
   if (m->n_nodes <= int64_t(kPtabIdMask))  // element node words (pipelined form of the linear level)
     if ((st = up(m->pl[1].ptab, node_words(E, 4, node_of, lconn1, 4), s)) != EBE_OK) return st;
-  {
-    std::vector<int32_t> cperm, cword;
-    colour_patches(m->n_nodes, t[0], cperm, m->pl[0].coff, cword);
-    if ((st = up(m->pl[0].cperm, cperm, s)) != EBE_OK) return st;
-    if ((st = up(m->pl[0].cword, cword, s)) != EBE_OK) return st;
-  }
+  std::vector<int32_t> cperm, cword;
+  colour_patches(m->n_nodes, t[0], cperm, m->pl[0].coff, cword);
+  if ((st = up(m->pl[0].cperm, cperm, s)) != EBE_OK) return st;
+  if ((st = up(m->pl[0].cword, cword, s)) != EBE_OK) return st;
   {
     // incidence lists of the quadratic patches: for each patch entry, the
     // element slots that touch it, in element order (deterministic form)
@@ -514,13 +630,20 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
     std::vector<uint32_t> fanw;
     build_fans(pelem[0], conn10, lconn, fix, pfan, fanw, felem);
     m->nfan = int64_t(felem.size()) / kFanLen;
-    if ((st = up(m->pfan, pfan, s)) != EBE_OK) return st;
-    if ((st = up(m->fanw, fanw, s)) != EBE_OK) return st;
-    if ((st = up(m->felem, felem, s)) != EBE_OK) return st;
     WideTables w[kWideSizes];
     parallel(kWideSizes, [&](int k) {
       build_wide(pelem[0], t[0], m->n_nodes, m->n_vertices, fix, pfan, fanw, k, w[k]);
     });
+    ChainTables c;
+    build_chains(t[0], m->n_nodes, fix, pfan, cword, fanw, c);
+    if ((st = up(m->pfan, pfan, s)) != EBE_OK) return st;
+    if ((st = up(m->fanw, fanw, s)) != EBE_OK) return st;
+    if ((st = up(m->felem, felem, s)) != EBE_OK) return st;
+    if ((st = up(m->cseq, c.seq, s)) != EBE_OK) return st;
+    if ((st = up(m->cslot, c.slot, s)) != EBE_OK) return st;
+    if ((st = up(m->croff, c.croff, s)) != EBE_OK) return st;
+    if ((st = up(m->crow, c.crow, s)) != EBE_OK) return st;
+    if ((st = up_level(m->chain, c.t, int64_t(c.seq.size()), s)) != EBE_OK) return st;
     for (int k = 0; k < kWideSizes; ++k) {
       ebe_mesh::Wide& d = m->wide[k];
       if ((st = up(d.pfan, w[k].pfan, s)) != EBE_OK) return st;

@@ -106,3 +106,33 @@ def test_wide_patches_of_ragged_meshes(gpu_lib, grid, dtype, nrhs):
         touched[np.unique(m.conn[(m.conn == node).any(axis=1)]), r] = True
     assert np.all(np.isfinite(y) | touched[:, None, :])
     assert not np.isfinite(y[0, :, 0]).any() and not np.isfinite(y[m.n_nodes - 1, :, nrhs - 1]).any()
+
+
+@pytest.fixture(scope="module")
+def long_mesh(gpu_lib):
+    """More than 768 patches to each of the eight ranges: chains of patches and single ones."""
+    m = meshgen.crust_mesh(53, 47, 25)
+    return m, ebe.Mesh.from_generated(m)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nrhs", [5, 16])
+def test_chains_of_patches(long_mesh, dtype, nrhs):
+    """Patches that hand accumulator rows on, on a mesh whose blocks do not end where chains do,
+    against the gather form, which takes each patch by itself."""
+    m, gm = long_mesh
+    dt = DT[dtype]
+    g = torch.Generator(device="cuda").manual_seed(94)
+    x, y0 = (torch.randn((m.n_nodes, 3, nrhs), generator=g, device="cuda", dtype=dt) for _ in range(2))
+
+    def products(form):
+        gm.set_form(0, dt, nrhs, form)
+        y = y0.clone()
+        gm.matvec_add(x, y)
+        return [v.double() for v in (gm.matvec(x), gm.matvec(x, apply_bc=True), y)]
+
+    ref = products(ebe.FORM_GATHER)
+    for form in (ebe.FORM_PIPELINED, ebe.FORM_COLOURED):
+        for k, (a, b) in enumerate(zip(products(form), ref)):
+            # both sum a few hundred products a row, which cancel to a tenth of their size
+            assert (a - b).abs().max() <= 100 * np.finfo(dtype).eps * b.abs().max(), (form, k)
