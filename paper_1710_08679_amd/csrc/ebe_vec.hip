@@ -6,17 +6,13 @@
 // touch consecutive addresses.
 #include <hip/hip_runtime.h>
 
-#include "ebe_internal.h"
+#include "patch_common.h"
 
 namespace ebe {
 namespace {
 
 constexpr int kBlock = 256;
 
-template <typename T, int VW>
-struct alignas(sizeof(T) * VW) VecT {
-  T v[VW];
-};
 
 inline unsigned grid_for(int64_t work) {
   int64_t g = (work + kBlock - 1) / kBlock;
@@ -33,7 +29,10 @@ constexpr int xfer_vec() {
   return v;
 }
 
-// y[N] = P1 x[Nv]: corners copied, edge node = mean of its two corners
+// y[N] = P1 x[Nv]: corners copied, edge node = mean of its two corners.  Bound
+// by the stores of y (88 MB on the 48x48x24 lattice, FP32 16 cases), which are
+// streaming ones: with the restriction below 65 -> 58 us.  XCD-contiguous
+// blocks, as the restriction takes them, made the pair 3 us slower here.
 template <typename T, int NR, bool BC>
 __global__ __launch_bounds__(kBlock) void k_prolong(const int32_t* __restrict__ ends,
                                                     const uint8_t* __restrict__ fix,
@@ -50,8 +49,9 @@ __global__ __launch_bounds__(kBlock) void k_prolong(const int32_t* __restrict__ 
     v = *reinterpret_cast<const V*>(x + node * W + off);
   } else {
     const int64_t k = node - n_vertices;
-    const V a = *reinterpret_cast<const V*>(x + int64_t(ends[2 * k]) * W + off);
-    const V b = *reinterpret_cast<const V*>(x + int64_t(ends[2 * k + 1]) * W + off);
+    const int2 e = reinterpret_cast<const int2*>(ends)[k];
+    const V a = *reinterpret_cast<const V*>(x + int64_t(e.x) * W + off);
+    const V b = *reinterpret_cast<const V*>(x + int64_t(e.y) * W + off);
 #pragma unroll
     for (int t = 0; t < VW; ++t) v.v[t] = T(0.5) * (a.v[t] + b.v[t]);
   }
@@ -59,10 +59,13 @@ __global__ __launch_bounds__(kBlock) void k_prolong(const int32_t* __restrict__ 
 #pragma unroll
     for (int t = 0; t < VW; ++t) v.v[t] = T(0);
   }
-  *reinterpret_cast<V*>(y + node * W + off) = v;
+  store_stream<T, VW>(y + node * W + off, v);
 }
 
-// y[Nv] = P1^T x[N]: corner value plus half of each incident edge-node value
+// y[Nv] = P1^T x[N]: corner value plus half of each incident edge-node value.
+// Bound by the latency of an index and then a row, about 14 times a corner:
+// four of them in flight took the pair (as above) from 75 to 66 us, and XCD-
+// contiguous blocks, whose corners share edge nodes, to 65.
 template <typename T, int NR, bool BC>
 __global__ __launch_bounds__(kBlock) void k_restrict(const int32_t* __restrict__ eoff,
                                                      const int32_t* __restrict__ idx,
@@ -71,14 +74,16 @@ __global__ __launch_bounds__(kBlock) void k_restrict(const int32_t* __restrict__
                                                      int64_t n_vertices) {
   constexpr int VW = xfer_vec<T, NR>(), W = 3 * NR, PR = W / VW;
   using V = VecT<T, VW>;
-  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const int64_t i = int64_t(xcd_patch(blockIdx.x, gridDim.x)) * kBlock + threadIdx.x;
   if (i >= n_vertices * PR) return;
   const int64_t v = i / PR;
   const int off = int(i - v * PR) * VW;
   T acc[VW];
 #pragma unroll
   for (int t = 0; t < VW; ++t) acc[t] = T(0);
-  for (int32_t k = eoff[v]; k < eoff[v + 1]; ++k) {
+  const int32_t k1 = eoff[v + 1];
+#pragma unroll 4
+  for (int32_t k = eoff[v]; k < k1; ++k) {
     const V e = *reinterpret_cast<const V*>(x + int64_t(idx[k]) * W + off);
 #pragma unroll
     for (int t = 0; t < VW; ++t) acc[t] += e.v[t];
