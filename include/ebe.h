@@ -101,7 +101,8 @@ typedef int32_t ebe_dtype;
  * most 8 (FP32) or 4 (FP64).
  * PIPELINED and COLOURED need a mesh below 2^25 nodes whose vectors at this
  * (dtype, nrhs) are below 4 GiB; elsewhere GATHER runs in their place.
- * AUTO: the mesh's tuned choice, else a fixed default. */
+ * AUTO: the mesh's tuned choice, else a default: GATHER, or PIPELINED on
+ * quadratic meshes of several thousand patches (48 elements each). */
 typedef enum {
   EBE_FORM_AUTO = -1,
   EBE_FORM_GATHER = 0,

@@ -704,7 +704,18 @@ bool form_usable(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs)
 int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   const int f = m->form[order == 2 ? 0 : 1][dt == EBE_F64 ? 0 : 1][nrhs];
   if (form_usable(m, order, f, dt, nrhs)) return f;
-  return EBE_FORM_GATHER;  // untuned: the form measured fastest on the reference workloads
+  // Untuned.  The pipelined form needs a few rounds of its resident workgroups
+  // to pay for its longer patches: from here on it measured faster at nearly
+  // every number of cases, below it slower at some.  Gather / pipelined, 29x23x17
+  // lattice (1417 patches): FP64 8 cases 36.1 / 35.1 us, 11 51.9 / 48.8, 16 55.9 /
+  // 52.5; FP32 5 24.2 / 25.0, 8 26.3 / 27.1, 16 34.7 / 33.6.  40x40x20 (4000): FP32 5
+  // 51.3 / 52.1, 8 55.8 / 47.2, 16 89.6 / 77.3; 1 case FP64 24.8 / 25.1, FP32 18.1 /
+  // 18.6.  64x64x40 (20480): FP64 1 98.9 / 71.7, 16 869 / 664; FP32 1 61.9 / 51.8, 5
+  // 266 / 233, 16 496 / 372.
+  const int64_t from = nrhs <= kWideCases ? 6000 : (dt == EBE_F64 ? 1280 : 3000);
+  if (order == 2 && m->pl[0].npatch >= from && form_usable(m, 2, EBE_FORM_PIPELINED, dt, nrhs))
+    return EBE_FORM_PIPELINED;
+  return EBE_FORM_GATHER;
 }
 
 hipError_t launch_ebe_form(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs, const void* x, void* y,

@@ -136,3 +136,22 @@ def test_chains_of_patches(long_mesh, dtype, nrhs):
         for k, (a, b) in enumerate(zip(products(form), ref)):
             # both sum a few hundred products a row, which cancel to a tenth of their size
             assert (a - b).abs().max() <= 100 * np.finfo(dtype).eps * b.abs().max(), (form, k)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nrhs", [1, 4, 7])
+def test_untuned_form_by_size(long_mesh, case, dtype, nrhs):
+    """Untuned, a mesh of many patches takes the pipelined form and a small one the gather form."""
+    dt = DT[dtype]
+    small = case[1]
+    small.set_form(0, dt, nrhs, ebe.FORM_AUTO)
+    assert small.form(0, dt, nrhs) == ebe.FORM_GATHER
+    m, gm = long_mesh
+    x = torch.randn((m.n_nodes, 3, nrhs), generator=torch.Generator(device="cuda").manual_seed(95), device="cuda",
+                    dtype=dt)
+    gm.set_form(0, dt, nrhs, ebe.FORM_GATHER)
+    ref = gm.matvec(x, apply_bc=True).double()
+    gm.set_form(0, dt, nrhs, ebe.FORM_AUTO)
+    assert gm.form(0, dt, nrhs) == ebe.FORM_PIPELINED
+    y = gm.matvec(x, apply_bc=True).double()
+    assert (y - ref).abs().max() <= 100 * np.finfo(dtype).eps * ref.abs().max()
