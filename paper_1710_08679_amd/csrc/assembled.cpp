@@ -32,12 +32,8 @@ namespace ebe {
 namespace {
 
 template <class T>
-ebe_status up(DBuf& b, const std::vector<T>& h, hipStream_t s) {
-  ebe_status st = b.alloc(std::max<size_t>(h.size(), 1) * sizeof(T));
-  if (st != EBE_OK) return st;
-  if (!h.empty())
-    EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-  return EBE_OK;
+ebe_status up(DBuf& b, const std::vector<T>& h, Uploads& s) {
+  return s.add(b, h.data(), h.size() * sizeof(T));
 }
 
 }  // namespace
@@ -70,7 +66,7 @@ ebe_status slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t
 }
 
 ebe_status upload_asm(AsmOp& op, int64_t rows, const std::vector<int32_t>& soff, const std::vector<int32_t>& scol,
-                      hipStream_t s) {
+                      Uploads& s) {
   ebe_status st = up(op.soff, soff, s);
   if (st == EBE_OK) st = up(op.col, scol, s);
   op.rows = rows;
@@ -80,7 +76,7 @@ ebe_status upload_asm(AsmOp& op, int64_t rows, const std::vector<int32_t>& soff,
 }
 
 ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std::vector<int32_t>& bcol,
-                        const uint8_t* fix, hipStream_t s) {
+                        const uint8_t* fix, Uploads& s) {
   const int64_t nv = int64_t(bptr.size()) - 1;
   // aggregation (the row of v in K1 is v and its neighbours)
   std::vector<int32_t> agg(nv, -1);

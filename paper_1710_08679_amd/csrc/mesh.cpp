@@ -45,13 +45,45 @@ ebe_status DBuf::alloc(size_t bytes) {
     return EBE_ERR_OOM;
   }
   n_ = bytes;
+  owned_ = true;
   return EBE_OK;
 }
 
+void DBuf::view(void* p, size_t bytes) {
+  release();
+  p_ = p;
+  n_ = bytes;
+}
+
 void DBuf::release() {
-  if (p_) (void)hipFree(p_);
+  if (p_ && owned_) (void)hipFree(p_);
   p_ = nullptr;
   n_ = 0;
+  owned_ = false;
+}
+
+ebe_status Uploads::add(DBuf& b, const void* host, size_t bytes) {
+  if (bytes > kSmall) {
+    ebe_status st = b.alloc(bytes);
+    if (st != EBE_OK) return st;
+    EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), host, bytes, hipMemcpyHostToDevice, s_));
+    return EBE_OK;
+  }
+  const size_t at = (host_.size() + 255) / 256 * 256;
+  host_.resize(at + std::max<size_t>(bytes, 1));
+  if (bytes && host) std::memcpy(host_.data() + at, host, bytes);
+  items_.push_back({&b, at, std::max<size_t>(bytes, 1)});
+  return EBE_OK;
+}
+
+ebe_status Uploads::finish(DBuf& owner) {
+  if (items_.empty()) return EBE_OK;
+  ebe_status st = owner.alloc(host_.size());
+  if (st != EBE_OK) return st;
+  EBE_TRY_HIP(hipMemcpyAsync(owner.as<void>(), host_.data(), host_.size(), hipMemcpyHostToDevice, s_));
+  for (const Item& i : items_) i.b->view(owner.as<char>() + i.at, i.bytes);
+  items_.clear();
+  return EBE_OK;
 }
 
 }  // namespace ebe
@@ -63,11 +95,8 @@ namespace {
 const int kEdge[6][2] = {{0, 1}, {1, 2}, {0, 2}, {0, 3}, {1, 3}, {2, 3}};
 
 template <class T>
-ebe_status upload(DBuf& b, const T* host, size_t count, hipStream_t s) {
-  ebe_status st = b.alloc(count * sizeof(T));
-  if (st != EBE_OK) return st;
-  EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), host, count * sizeof(T), hipMemcpyHostToDevice, s));
-  return EBE_OK;
+ebe_status upload(DBuf& b, const T* host, size_t count, Uploads& s) {
+  return s.add(b, host, count * sizeof(T));
 }
 
 bool material_ok(double E, double nu) {
@@ -327,21 +356,23 @@ static ebe_status create_mesh(const char* fn, bool curved, const double* xyz, in
   m->curved = curved;
   (void)hipGetDevice(&m->device);
   ebe_status st = EBE_OK;
-  if (st == EBE_OK) st = upload(m->conn, packed.data(), packed.size(), s);
-  if (st == EBE_OK) st = upload(m->xv, xv.data(), xv.size(), s);
-  if (st == EBE_OK) st = upload(m->young, young, size_t(E), s);
-  if (st == EBE_OK) st = upload(m->poisson, poisson, size_t(E), s);
-  if (st == EBE_OK) st = upload(m->fix, fix.data(), fix.size(), s);
-  if (st == EBE_OK) st = upload(m->edge_ends, ends.data(), std::max<size_t>(ends.size(), 1), s);
-  if (st == EBE_OK) st = upload(m->v2e_off, off.data(), off.size(), s);
-  if (st == EBE_OK) st = upload(m->v2e_idx, idx.data(), std::max<size_t>(idx.size(), 1), s);
-  if (st == EBE_OK) st = upload(m->v2el_off, veoff.data(), veoff.size(), s);
-  if (st == EBE_OK) st = upload(m->v2el, vel.data(), vel.size(), s);
-  if (st == EBE_OK) st = upload_asm(m->k1, Nv, soff, scol, s);
-  if (st == EBE_OK) st = build_level2(m, bptr, bcol, fix.data(), s);
+  Uploads up(s);
+  if (st == EBE_OK) st = upload(m->conn, packed.data(), packed.size(), up);
+  if (st == EBE_OK) st = upload(m->xv, xv.data(), xv.size(), up);
+  if (st == EBE_OK) st = upload(m->young, young, size_t(E), up);
+  if (st == EBE_OK) st = upload(m->poisson, poisson, size_t(E), up);
+  if (st == EBE_OK) st = upload(m->fix, fix.data(), fix.size(), up);
+  if (st == EBE_OK) st = upload(m->edge_ends, ends.data(), std::max<size_t>(ends.size(), 1), up);
+  if (st == EBE_OK) st = upload(m->v2e_off, off.data(), off.size(), up);
+  if (st == EBE_OK) st = upload(m->v2e_idx, idx.data(), std::max<size_t>(idx.size(), 1), up);
+  if (st == EBE_OK) st = upload(m->v2el_off, veoff.data(), veoff.size(), up);
+  if (st == EBE_OK) st = upload(m->v2el, vel.data(), vel.size(), up);
+  if (st == EBE_OK) st = upload_asm(m->k1, Nv, soff, scol, up);
+  if (st == EBE_OK) st = build_level2(m, bptr, bcol, fix.data(), up);
   if (st == EBE_OK) st = m->lame64.alloc(size_t(E) * 2 * sizeof(double));
   if (st == EBE_OK) st = m->lame32.alloc(size_t(E) * 2 * sizeof(float));
-  if (st == EBE_OK) st = build_patches(m, conn10, fix.data(), s);
+  if (st == EBE_OK) st = build_patches(m, conn10, fix.data(), up);
+  if (st == EBE_OK) st = up.finish(m->small_tables);
   if (st == EBE_OK) st = m->gacc.alloc(kGammaBytes);
   if (st == EBE_OK) {
     hipError_t he = launch_lame(m, s);

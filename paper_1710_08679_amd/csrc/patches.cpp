@@ -274,11 +274,47 @@ void build_fans(const std::vector<int32_t>& pelem, const int32_t* conn10, const 
   pfan.assign(npatch + 1, 0);
   auto first = [&](int t) { return npatch * t / nthread; };
   parallel(nthread, [&](int t) {
+    // a patch's fans depend only on which corners its elements share: on a
+    // lattice most patches repeat one of a few patterns
+    struct Pattern {
+      std::vector<uint8_t> key;  // the elements' corners, numbered by first appearance
+      std::vector<Fan> fans;     // elements relative to the patch's first
+    };
+    std::vector<Pattern> seen;
+    size_t oldest = 0;
+    std::vector<uint8_t> key;
     for (int64_t p = first(t); p < first(t + 1); ++p) {
-      const size_t f0 = part[t].size();
-      fans_of_patch(pelem[p], pelem[p + 1] - pelem[p], conn10, part[t]);
-      std::stable_sort(part[t].begin() + f0, part[t].end(), [](const Fan& a, const Fan& b) { return a.len > b.len; });
-      pfan[p + 1] = int32_t(part[t].size() - f0);
+      const int32_t e0 = pelem[p], ne = pelem[p + 1] - e0;
+      key.resize(size_t(ne) * 4);
+      int16_t number[256];
+      std::fill(number, number + 256, int16_t(-1));
+      int16_t n = 0;
+      for (int32_t el = 0; el < ne; ++el)
+        for (int a = 0; a < 4; ++a) {
+          int16_t& v = number[lconn[(size_t(e0) + el) * 16 + a]];
+          if (v < 0) v = n++;
+          key[size_t(el) * 4 + a] = uint8_t(v);
+        }
+      const Pattern* same = nullptr;
+      for (const Pattern& q : seen)
+        if (q.key == key) same = &q;
+      if (!same) {
+        if (seen.size() < 16) seen.emplace_back();
+        Pattern& q = seen[oldest];
+        oldest = (oldest + 1) % 16;
+        q.key = key;
+        q.fans.clear();
+        fans_of_patch(e0, ne, conn10, q.fans);
+        std::stable_sort(q.fans.begin(), q.fans.end(), [](const Fan& a, const Fan& b) { return a.len > b.len; });
+        for (Fan& f : q.fans)
+          for (int i = 0; i < f.len; ++i) f.elem[i] -= e0;
+        same = &q;
+      }
+      for (Fan f : same->fans) {
+        for (int i = 0; i < f.len; ++i) f.elem[i] += e0;
+        part[t].push_back(f);
+      }
+      pfan[p + 1] = int32_t(same->fans.size());
     }
   });
   for (int64_t p = 0; p < npatch; ++p) pfan[p + 1] += pfan[p];
@@ -551,15 +587,11 @@ void colour_patches(int64_t n_nodes, const LevelTables& t, std::vector<int32_t>&
 }
 
 template <class T>
-ebe_status up(DBuf& b, const std::vector<T>& h, hipStream_t s) {
-  ebe_status st = b.alloc(std::max<size_t>(h.size(), 1) * sizeof(T));
-  if (st != EBE_OK) return st;
-  if (!h.empty())
-    EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-  return EBE_OK;
+ebe_status up(DBuf& b, const std::vector<T>& h, Uploads& s) {
+  return s.add(b, h.data(), h.size() * sizeof(T));
 }
 
-ebe_status up_level(PatchLevel& L, const LevelTables& t, int64_t npatch, hipStream_t s) {
+ebe_status up_level(PatchLevel& L, const LevelTables& t, int64_t npatch, Uploads& s) {
   ebe_status st = EBE_OK;
   if ((st = up(L.poff, t.poff, s)) != EBE_OK) return st;
   if ((st = up(L.pnode, t.pnode, s)) != EBE_OK) return st;
@@ -576,17 +608,32 @@ ebe_status up_level(PatchLevel& L, const LevelTables& t, int64_t npatch, hipStre
 
 }  // namespace
 
-ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix, hipStream_t s) {
+ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix, Uploads& s) {
   const int64_t E = m->n_elem;
   auto node_of = [&](int64_t e, int a) { return conn10[size_t(e) * 10 + a]; };
-  // 1. cut elements into patches, separately for each level
-  std::vector<int32_t> pelem[2] = {cut_patches(E, 10, m->n_nodes, kPatchElems, kPatchNodes, node_of),
-                                   cut_patches(E, 4, m->n_vertices, kLinPatchElems, kLinPatchCorners, node_of)};
-  // 2. quadratic level (all 10 nodes) and linear level (corners)
+  // two independent halves of the work, side by side on meshes that repay a thread
+  auto both = [&](auto&& f) {
+    if (E >= 65536) {
+      parallel(2, f);
+    } else {
+      f(0);
+      f(1);
+    }
+  };
+  // 1. cut elements into patches, separately for each level: 2. the quadratic
+  // one (all 10 nodes) and the linear one (corners)
+  std::vector<int32_t> pelem[2];
   std::vector<uint8_t> lconn(size_t(E) * 16, 0), lconn1(size_t(E) * 4, 0);
   LevelTables t[2];
-  build_level(pelem[0], 10, m->n_nodes, fix, node_of, lconn, 16, t[0]);
-  build_level(pelem[1], 4, m->n_vertices, fix, node_of, lconn1, 4, t[1]);
+  both([&](int l) {
+    if (l == 0) {
+      pelem[0] = cut_patches(E, 10, m->n_nodes, kPatchElems, kPatchNodes, node_of);
+      build_level(pelem[0], 10, m->n_nodes, fix, node_of, lconn, 16, t[0]);
+    } else {
+      pelem[1] = cut_patches(E, 4, m->n_vertices, kLinPatchElems, kLinPatchCorners, node_of);
+      build_level(pelem[1], 4, m->n_vertices, fix, node_of, lconn1, 4, t[1]);
+    }
+  });
   if (t[0].max_nodes > kPatchNodes || t[1].max_nodes > kLinPatchCorners) {
     set_error("build_patches: patch with %d nodes / %d corners exceeds %d / %d", t[0].max_nodes, t[1].max_nodes,
               kPatchNodes, kLinPatchCorners);
@@ -597,45 +644,48 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
   if ((st = up(m->lconn1, lconn1, s)) != EBE_OK) return st;
   if (m->n_nodes <= int64_t(kPtabIdMask))  // element node words (pipelined form of the linear level)
     if ((st = up(m->pl[1].ptab, node_words(E, 4, node_of, lconn1, 4), s)) != EBE_OK) return st;
-  std::vector<int32_t> cperm, cword;
-  colour_patches(m->n_nodes, t[0], cperm, m->pl[0].coff, cword);
+  std::vector<int32_t> cperm, cword, pistart, pfan, felem;
+  std::vector<uint16_t> pinc;
+  std::vector<uint32_t> fanw;
+  WideTables w[kWideSizes];
+  const bool fans = m->n_nodes <= int64_t(kPtabIdMask) && !m->curved;  // pipelined and coloured forms
+  both([&](int k) {
+    if (k == 0) {
+      colour_patches(m->n_nodes, t[0], cperm, m->pl[0].coff, cword);
+      // incidence lists of the quadratic patches: for each patch entry, the
+      // element slots that touch it, in element order (deterministic form)
+      const std::vector<int32_t>& pe = pelem[0];
+      const LevelTables& t0 = t[0];
+      pinc.resize(size_t(E) * 10);
+      pistart.resize(t0.pnode.size());
+      std::vector<int32_t> cnt;
+      for (size_t p = 0; p + 1 < pe.size(); ++p) {
+        const int32_t e0 = pe[p], ne = pe[p + 1] - e0, o0 = t0.poff[p], nn = t0.poff[p + 1] - o0;
+        cnt.assign(size_t(nn) + 1, 0);
+        for (int32_t el = 0; el < ne; ++el)
+          for (int a = 0; a < 10; ++a) cnt[lconn[(size_t(e0) + el) * 16 + a] + 1]++;
+        for (int32_t i = 0; i < nn; ++i) cnt[i + 1] += cnt[i];
+        for (int32_t i = 0; i < nn; ++i) pistart[size_t(o0) + i] = cnt[i];
+        for (int32_t el = 0; el < ne; ++el)
+          for (int a = 0; a < 10; ++a) {
+            const int lid = lconn[(size_t(e0) + el) * 16 + a];
+            pinc[size_t(e0) * 10 + cnt[lid]++] = uint16_t(el * 10 + a);
+          }
+      }
+    } else if (fans) {
+      build_fans(pelem[0], conn10, lconn, fix, pfan, fanw, felem);
+      static_assert(kWideSizes == 2, "");
+      both([&](int i) { build_wide(pelem[0], t[0], m->n_nodes, m->n_vertices, fix, pfan, fanw, i, w[i]); });
+    }
+  });
   if ((st = up(m->pl[0].cperm, cperm, s)) != EBE_OK) return st;
   if ((st = up(m->pl[0].cword, cword, s)) != EBE_OK) return st;
-  {
-    // incidence lists of the quadratic patches: for each patch entry, the
-    // element slots that touch it, in element order (deterministic form)
-    const std::vector<int32_t>& pe = pelem[0];
-    const LevelTables& t0 = t[0];
-    std::vector<uint16_t> pinc(size_t(E) * 10);
-    std::vector<int32_t> pistart(t0.pnode.size());
-    std::vector<int32_t> cnt;
-    for (size_t p = 0; p + 1 < pe.size(); ++p) {
-      const int32_t e0 = pe[p], ne = pe[p + 1] - e0, o0 = t0.poff[p], nn = t0.poff[p + 1] - o0;
-      cnt.assign(size_t(nn) + 1, 0);
-      for (int32_t el = 0; el < ne; ++el)
-        for (int a = 0; a < 10; ++a) cnt[lconn[(size_t(e0) + el) * 16 + a] + 1]++;
-      for (int32_t i = 0; i < nn; ++i) cnt[i + 1] += cnt[i];
-      for (int32_t i = 0; i < nn; ++i) pistart[size_t(o0) + i] = cnt[i];
-      for (int32_t el = 0; el < ne; ++el)
-        for (int a = 0; a < 10; ++a) {
-          const int lid = lconn[(size_t(e0) + el) * 16 + a];
-          pinc[size_t(e0) * 10 + cnt[lid]++] = uint16_t(el * 10 + a);
-        }
-    }
-    if ((st = up(m->pl[0].pinc, pinc, s)) != EBE_OK) return st;
-    if ((st = up(m->pl[0].pistart, pistart, s)) != EBE_OK) return st;
-  }
-  if (m->n_nodes <= int64_t(kPtabIdMask) && !m->curved) {  // fans (pipelined and coloured forms)
-    std::vector<int32_t> pfan, felem;
-    std::vector<uint32_t> fanw;
-    build_fans(pelem[0], conn10, lconn, fix, pfan, fanw, felem);
-    m->nfan = int64_t(felem.size()) / kFanLen;
-    WideTables w[kWideSizes];
-    parallel(kWideSizes, [&](int k) {
-      build_wide(pelem[0], t[0], m->n_nodes, m->n_vertices, fix, pfan, fanw, k, w[k]);
-    });
+  if ((st = up(m->pl[0].pinc, pinc, s)) != EBE_OK) return st;
+  if ((st = up(m->pl[0].pistart, pistart, s)) != EBE_OK) return st;
+  if (fans) {
     ChainTables c;
     build_chains(t[0], m->n_nodes, fix, pfan, cword, fanw, c);
+    m->nfan = int64_t(felem.size()) / kFanLen;
     if ((st = up(m->pfan, pfan, s)) != EBE_OK) return st;
     if ((st = up(m->fanw, fanw, s)) != EBE_OK) return st;
     if ((st = up(m->felem, felem, s)) != EBE_OK) return st;
