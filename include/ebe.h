@@ -102,7 +102,8 @@ typedef int32_t ebe_dtype;
  * PIPELINED and COLOURED need a mesh below 2^25 nodes whose vectors at this
  * (dtype, nrhs) are below 4 GiB; elsewhere GATHER runs in their place.
  * AUTO: the mesh's tuned choice, else a default: GATHER, or PIPELINED on
- * quadratic meshes of several thousand patches (48 elements each). */
+ * quadratic meshes of several thousand patches (48 elements each), or of up
+ * to 384 elements at one or two cases. */
 typedef enum {
   EBE_FORM_AUTO = -1,
   EBE_FORM_GATHER = 0,

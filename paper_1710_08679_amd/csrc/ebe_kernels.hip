@@ -713,7 +713,11 @@ int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   // 18.6.  64x64x40 (20480): FP64 1 98.9 / 71.7, 16 869 / 664; FP32 1 61.9 / 51.8, 5
   // 266 / 233, 16 496 / 372.
   const int64_t from = nrhs <= kWideCases ? 6000 : (dt == EBE_F64 ? 1280 : 3000);
-  if (order == 2 && m->pl[0].npatch >= from && form_usable(m, 2, EBE_FORM_PIPELINED, dt, nrhs))
+  // A mesh that is one wide patch has no shared nodes and so one launch instead
+  // of two: 4^3 cube, 1 case FP64 12.4 / 10.2 us, FP32 11.9 / 10.2, 2 cases 12.8 /
+  // 9.9 and 12.7 / 10.3 (3 and 4 cases: 12.8 / 16.8 and 13.1 / 14.0).
+  const bool one = nrhs <= 2 && m->nfan > 0 && m->wide[wide_size(dt == EBE_F64 ? 8 : 4, nrhs)].pl.nshared == 0;
+  if (order == 2 && (one || m->pl[0].npatch >= from) && form_usable(m, 2, EBE_FORM_PIPELINED, dt, nrhs))
     return EBE_FORM_PIPELINED;
   return EBE_FORM_GATHER;
 }

@@ -140,12 +140,13 @@ def test_chains_of_patches(long_mesh, dtype, nrhs):
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("nrhs", [1, 4, 7])
-def test_untuned_form_by_size(long_mesh, case, dtype, nrhs):
-    """Untuned, a mesh of many patches takes the pipelined form and a small one the gather form."""
+def test_untuned_form_by_size(long_mesh, dtype, nrhs):
+    """Untuned, a mesh of many patches takes the pipelined form and a small one
+    the gather form, except at 1 or 2 cases where it is a single wide patch."""
     dt = DT[dtype]
-    small = case[1]
-    small.set_form(0, dt, nrhs, ebe.FORM_AUTO)
-    assert small.form(0, dt, nrhs) == ebe.FORM_GATHER
+    assert ebe.Mesh.from_generated(parity_mesh(9, 5, 7, seed=6)).form(0, dt, nrhs) == ebe.FORM_GATHER
+    one = ebe.Mesh.from_generated(parity_mesh(4, 4, 4, seed=6)).form(0, dt, nrhs)
+    assert one == (ebe.FORM_PIPELINED if nrhs <= 2 else ebe.FORM_GATHER)
     m, gm = long_mesh
     x = torch.randn((m.n_nodes, 3, nrhs), generator=torch.Generator(device="cuda").manual_seed(95), device="cuda",
                     dtype=dt)
