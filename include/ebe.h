@@ -79,7 +79,8 @@ typedef int32_t ebe_dtype;
  * PIPELINED is GATHER in persistent workgroups that fetch the next patch's
  * metadata while computing the current one (on the quadratic level with the
  * patch's tetrahedra taken in fans around common edges, so nodes that
- * neighbouring tetrahedra share are read and added once); ASSEMBLED (linear level only)
+ * neighbouring tetrahedra share are read and added once, and at up to four
+ * cases on wider patches, one workgroup each); ASSEMBLED (linear level only)
  * applies K1 assembled once (per material) into 3x3 blocks over the corner
  * graph instead of forming element products, so a product reads each block
  * once for all cases: a departure from the paper's element-by-element

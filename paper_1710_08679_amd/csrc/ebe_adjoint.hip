@@ -30,7 +30,8 @@ constexpr int kBlock = 256;
 template <typename T, int NR>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3))) void k_adjoint_fan(
     const uint32_t* __restrict__ fanw, const int32_t* __restrict__ felem, const double4* __restrict__ xv,
-    const double* __restrict__ young, const typename Pair<T>::type* __restrict__ lame, const T* __restrict__ u, const T* __restrict__ lam, T* __restrict__ g,
+    const double* __restrict__ young, const typename Pair<T>::type* __restrict__ lame, const T* __restrict__ u,
+    const T* __restrict__ lam, T* __restrict__ g,
     int64_t nfan) {
   constexpr int G = 64 / NR;  // fans per wavefront
   constexpr int HALF = NR > 8 ? 8 : (NR > 4 ? 4 : (NR > 2 ? 2 : 1));
@@ -128,7 +129,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
 }
 
 template <typename T, int NR>
-void launch_adjoint_fan(const ebe_mesh* m, const typename Pair<T>::type* lame, const T* u, const T* lam, T* g, hipStream_t s) {
+void launch_adjoint_fan(const ebe_mesh* m, const typename Pair<T>::type* lame, const T* u, const T* lam, T* g,
+                        hipStream_t s) {
   constexpr int per_block = (kBlock / 64) * (64 / NR);
   hipLaunchKernelGGL((k_adjoint_fan<T, NR>), dim3(unsigned((m->nfan + per_block - 1) / per_block)), dim3(kBlock), 0,
                      s, m->fanw.as<uint32_t>(), m->felem.as<int32_t>(), m->xv.as<double4>(), m->young.as<double>(),

@@ -41,7 +41,8 @@ template <typename T, int NR, bool MASK, bool GAMMA>
 __global__ __launch_bounds__(wide_threads<T>(NR)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3))) void
 k_ebe_wide(const uint16_t* __restrict__ fanl, const int32_t* __restrict__ felem, const int32_t* __restrict__ pfan,
            const int32_t* __restrict__ pcorner, const int32_t* __restrict__ poff, const int32_t* __restrict__ pnode,
-           const int32_t* __restrict__ pslot, const double4* __restrict__ xv, const typename Pair<T>::type* __restrict__ lame, const T* __restrict__ x,
+           const int32_t* __restrict__ pslot, const double4* __restrict__ xv,
+           const typename Pair<T>::type* __restrict__ lame, const T* __restrict__ x,
            T* __restrict__ y, T* __restrict__ stage, int stream, int bc, int add, double* __restrict__ gamma,
            double* __restrict__ gslot, unsigned* __restrict__ gcount, const int* __restrict__ gate) {
   constexpr int W = 3 * NR;

@@ -23,9 +23,9 @@
 //      accumulator F, so the element phase adds only its case offset);
 //   B. issue the next patch's loads;
 //   C. element phase: one work-item per (fan, case);
-//   D. write back the finished nodes, zeroing F behind it: exclusive nodes straight into y,
-//      shared nodes as partial sums into their staging slots (a node-centric
-//      pass adds them after).
+//   D. write back the finished nodes, zeroing F behind it: exclusive nodes
+//      straight into y, shared nodes as partial sums into their staging slots
+//      (a node-centric pass adds them after).
 //
 // Coloured form: the patches are coloured so that no two patches of a colour
 // share a node, and the colours run one launch after another.  A patch writes
@@ -72,7 +72,9 @@ constexpr int fan_threads(int nr) {
   const int want = nr % 4 == 0 ? fans * nr : ((fans + g - 1) / g * g * nr + 63) / 64 * 64;
   return want > 256 ? 256 : want;
 }
-constexpr int fan_lds_bytes(int nr) { return kPatchNodes * 3 * nr * 8 + kFanCap * kFanStride * 8 + 9 * kPatchNodes + 8 * nr + 16; }
+constexpr int fan_lds_bytes(int nr) {
+  return kPatchNodes * 3 * nr * 8 + kFanCap * kFanStride * 8 + 9 * kPatchNodes + 8 * nr + 16;
+}
 // Wavefronts per SIMD that the LDS of a workgroup leaves room for, at most
 // three in FP32 (168 registers: three tetrahedra's shared sums stay in
 // registers) and two in FP64 (256).
@@ -99,15 +101,16 @@ __device__ __forceinline__ double row_value(double v) {
 // GAMMA: also form gamma[r] += (x_r, K x_r), what CG needs from q = K p (never
 // with add), as the sum of each tetrahedron's forces times its nodal values,
 // which are still at hand (from strains and stresses it took more
-// instructions, and registers that made the FP64 kernel spill).  MASK: zero the fixed DOFs of x while reading it.  COLOUR:
-// the coloured form.  plist lists this launch's patches: all of them
+// instructions, and registers that made the FP64 kernel spill).  MASK: zero
+// the fixed DOFs of x while reading it.  COLOUR: the coloured form.  plist lists this launch's patches: all of them
 // in chain order, the node entries being by place in it, or one colour, the
 // entries being by patch.
 template <typename T, int NR, bool MASK, bool GAMMA, bool COLOUR>
 __global__ __launch_bounds__(fan_threads<T>(NR)) __attribute__((amdgpu_waves_per_eu(fan_waves_per_simd<T>(NR)))) void
 k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const int32_t* __restrict__ pfan,
           const int32_t* __restrict__ poff, const int32_t* __restrict__ pnode, const int32_t* __restrict__ pslot,
-          const uint8_t* __restrict__ prow, const int32_t* __restrict__ plist, const T* __restrict__ x, T* __restrict__ y, T* __restrict__ stage,
+          const uint8_t* __restrict__ prow, const int32_t* __restrict__ plist, const T* __restrict__ x,
+          T* __restrict__ y, T* __restrict__ stage,
           int stream, int npatch, int bc, int add, double* __restrict__ gamma, double* __restrict__ gslot,
           unsigned* __restrict__ gcount, const int* __restrict__ gate) {
   constexpr int W = 3 * NR;                         // values of a node row
@@ -460,7 +463,8 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
       if (ent < cnn) {
         const int32_t wd = words[ent];  
         const bool fixed = bc && ((wd >> (kIdxBits + sc)) & 1);
-        if (((!GAMMA && add && wd != kNoEntry) || wd < 0) && !fixed) old[k] = yv[uint32_t(wd & kIdxMask) * uint32_t(NV) + uint32_t(sv)];
+        if (((!GAMMA && add && wd != kNoEntry) || wd < 0) && !fixed)
+          old[k] = yv[uint32_t(wd & kIdxMask) * uint32_t(NV) + uint32_t(sv)];
       }
     }
 #pragma unroll
@@ -577,7 +581,8 @@ hipError_t launch_fan(const ebe_mesh* m, const void* x, void* y, bool mask_in, b
     // last-level cache until the shared-node pass reads them back
     const PatchLevel& L = m->chain;
     const bool st = int64_t(L.nslots) * 3 * NR * int64_t(sizeof(T)) > kStreamStageBytes;
-    hipError_t e = launch_fan_c<T, NR, false>(m, m->cseq.as<int32_t>(), L.npatch, x, y, st, mask_in, bc, add, gate, s, gamma);
+    hipError_t e = launch_fan_c<T, NR, false>(m, m->cseq.as<int32_t>(), L.npatch, x, y, st, mask_in, bc, add, gate, s,
+                                              gamma);
     if (e != hipSuccess || L.nshared == 0) return e;
     const int64_t work = L.nshared * (3 * NR / reduce_width<T, NR>());
     hipLaunchKernelGGL((k_reduce_shared<T, NR>), dim3(unsigned((work + 255) / 256)), dim3(256), 0, s,

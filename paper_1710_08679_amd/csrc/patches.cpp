@@ -530,7 +530,8 @@ void build_wide(const std::vector<int32_t>& pelem, const LevelTables& t0, int64_
     w.pfan.push_back(pfan[p1]);
     w.pcorner.push_back(nc);
   }
-  for (size_t i = 0; i + 1 < w.t.poff.size(); ++i) w.t.max_nodes = std::max(w.t.max_nodes, w.t.poff[i + 1] - w.t.poff[i]);
+  for (size_t i = 0; i + 1 < w.t.poff.size(); ++i)
+    w.t.max_nodes = std::max(w.t.max_nodes, w.t.poff[i + 1] - w.t.poff[i]);
   stage_level(n_nodes, fix, count, w.t);
 }
 
