@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
              : a == 5 ? s[2][c] : a == 6 ? s[1][c] : a == 7 ? n[1][c] : a == 8 ? n[2][c] : m[c];
       };
       T unused = T(0);
-      p2_apply<T>(
+      p2_apply(
           Gm, cl, cm, [&](int a, int c) -> T { return pick(ud, us, un, ur, a, c); },
           [&](int a, const T fv[3]) {
 #pragma unroll
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_loop(const int32_t* __restri
   T acc = T(0);
   for (int r = 0; r < nrhs; ++r) {
     T unused = T(0);
-    p2_apply<T>(
+    p2_apply(
         G, T(lm.x) * s, T(lm.y) * s,
         [&](int a, int c) -> T {
           return ((cw[a] >> (kIdxBits + c)) & 1) ? T(0) : u[size_t(cw[a] & kIdxMask) * 3 * nrhs + c * nrhs + r];

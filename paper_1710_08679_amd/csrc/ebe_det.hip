@@ -149,7 +149,7 @@ __attribute__((amdgpu_waves_per_eu(det_waves_per_simd<T>(NR)))) void k_ebe_det(
 #pragma unroll
         for (int c = 0; c < 3; ++c) eb[a * SL + c * CW] = f[c];
       };
-      p2_apply<T>(G, cl, cm, u, emit, gamma != nullptr, en);
+      p2_apply(G, cl, cm, u, emit, gamma != nullptr, en);
       if (gamma) {
         if constexpr (kLaneCase) en_acc += double(en);
         else atomicAdd(&gsum[c0 + r], double(en));

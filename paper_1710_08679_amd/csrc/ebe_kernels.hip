@@ -217,7 +217,7 @@ __attribute__((amdgpu_waves_per_eu(patch_waves_per_simd<T>(NR, ORDER, STAGE, CUR
 #pragma unroll
           for (int d = 0; d < 3; ++d) G[k][d] = geo[el][3 * k + d];
         const T cl = geo[el][12], cm = geo[el][13];
-        if constexpr (ORDER == 2) p2_apply<T>(G, cl, cm, u, emit, gamma != nullptr, en);
+        if constexpr (ORDER == 2) p2_apply(G, cl, cm, u, emit, gamma != nullptr, en);
         else p1_apply<T>(G, cl, cm, u, emit, gamma != nullptr, en);
       }
       if (gamma) {

@@ -183,7 +183,10 @@ k_ebe_wide(const uint16_t* __restrict__ fanl, const int32_t* __restrict__ felem,
       auto emit = [&](int a, const T fv[3]) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          if constexpr (GAMMA) en += fv[c] * u(a, c);
+          if constexpr (GAMMA) {  // as in fan_kernel.h
+            if (a == 0) asm volatile("" : "+v"(ud[0][c]));
+            else en += fv[c] * (u(a, c) - ud[0][c]);
+          }
           const double d = double(fv[c]);
           if (a == 0 || a == 1 || a == 4) {
             fd[a == 4 ? 2 : a][c] += d;
@@ -198,7 +201,7 @@ k_ebe_wide(const uint16_t* __restrict__ fanl, const int32_t* __restrict__ felem,
         }
       };
       T unused = T(0);
-      p2_apply<T>(Gm, cl, cm, u, emit, false, unused);
+      p2_apply(Gm, cl, cm, u, emit, false, unused);
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll

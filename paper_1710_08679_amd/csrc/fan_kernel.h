@@ -77,12 +77,13 @@ constexpr int fan_lds_bytes(int nr) {
 }
 // Wavefronts per SIMD that the LDS of a workgroup leaves room for, at most
 // three in FP32 (168 registers: three tetrahedra's shared sums stay in
-// registers) and two in FP64 (256).
+// registers) and two in FP64 (256; by tetrahedra with (x, K x) three, which
+// left to itself takes as many registers as two allow).
 template <typename T>
-constexpr int fan_waves_per_simd(int nr) {
+constexpr int fan_waves_per_simd(int nr, bool gamma) {
   const int wg = 163840 / ((fan_lds_bytes(nr) + 1279) / 1280 * 1280);
   const int w = (wg * (fan_threads<T>(nr) / 64) + 3) / 4;
-  const int most = sizeof(T) == 8 ? 2 : (fan_singles<T>(nr) ? 4 : 3);
+  const int most = sizeof(T) == 8 ? (gamma && fan_singles<T>(nr) ? 3 : 2) : (fan_singles<T>(nr) ? 4 : 3);
   return w > most ? most : (w < 1 ? 1 : w);
 }
 
@@ -99,14 +100,21 @@ __device__ __forceinline__ double row_value(double v) {
 }
 
 // GAMMA: also form gamma[r] += (x_r, K x_r), what CG needs from q = K p (never
-// with add), as the sum of each tetrahedron's forces times its nodal values,
-// which are still at hand (from strains and stresses it took more
-// instructions, and registers that made the FP64 kernel spill).  MASK: zero
-// the fixed DOFs of x while reading it.  COLOUR: the coloured form.  plist lists this launch's patches: all of them
-// in chain order, the node entries being by place in it, or one colour, the
-// entries being by patch.
+// with add), free of the rounding that a translation common to a tetrahedron's
+// nodes would bring in: from the nodes' differences from corner p (in FP32 the
+// error of the plain sum of force times nodal value was twice to eight times
+// that of the gather form's strains).  By tetrahedra: strains and stresses of the
+// differences (force times value read x twice: 64x64x40 lattice, FP64 12 cases
+// 1168 us, FP32 9 cases 514; now 646 and 455).  By fans, where that took more
+// instructions and registers that made the FP64 kernel spill: forces times
+// differences, which FP64 takes as it reads x (kShift: p's own terms fall away,
+// 670 us at 16 cases against 732) and FP32 as it sums (376 us against 386;
+// without (x, K x) 367).
+// MASK: zero the fixed DOFs of x while reading it.  COLOUR: the coloured form.
+// plist lists this launch's patches: all of them in chain order, the node
+// entries being by place in it, or one colour, the entries being by patch.
 template <typename T, int NR, bool MASK, bool GAMMA, bool COLOUR>
-__global__ __launch_bounds__(fan_threads<T>(NR)) __attribute__((amdgpu_waves_per_eu(fan_waves_per_simd<T>(NR)))) void
+__global__ __launch_bounds__(fan_threads<T>(NR)) __attribute__((amdgpu_waves_per_eu(fan_waves_per_simd<T>(NR, GAMMA)))) void
 k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const int32_t* __restrict__ pfan,
           const int32_t* __restrict__ poff, const int32_t* __restrict__ pnode, const int32_t* __restrict__ pslot,
           const uint8_t* __restrict__ prow, const int32_t* __restrict__ plist, const T* __restrict__ x,
@@ -129,6 +137,7 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
   constexpr int GV = 16 / int(sizeof(T));
   constexpr bool kTouch = !COLOUR && (sizeof(T) == 8 || fan_singles<T>(NR));
   constexpr bool kRowLane = NR == 16 && sizeof(T) == 8;
+  constexpr bool kShift = GAMMA && sizeof(T) == 8;
   using V = VecT<T, VEC>;
   using GR = VecT<T, GV>;
   __shared__ double F[MAXN * W];
@@ -283,9 +292,19 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
               else if (k == 1) cm = gv.v[t];
             }
           }
+          auto value = [&](int a, int c) -> T {
+            return *reinterpret_cast<const T*>(xb + size_t(xo[a]) + size_t(c) * NR * sizeof(T));
+          };
+          T up[3];
+          if constexpr (GAMMA) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) up[c] = value(0, c);
+          }
           auto u = [&](int a, int c) -> T {
-            const T v = *reinterpret_cast<const T*>(xb + size_t(xo[a]) + size_t(c) * NR * sizeof(T));
-            if constexpr (MASK) {
+            const T v = value(a, c);
+            if constexpr (GAMMA) {
+              return v - up[c];
+            } else if constexpr (MASK) {
               const int wa = a == 0 ? 0 : a == 1 ? 1 : a == 4 ? 2 : a == 2 ? (i == 0 ? 3 : 2 + 4 * i)
                            : a == 6 ? (i == 0 ? 4 : 3 + 4 * i) : a == 5 ? (i == 0 ? 5 : 4 + 4 * i)
                            : a == 3 ? 6 + 4 * i : a == 9 ? 9 + 4 * i : a + 4 * i;  // (7, 8)
@@ -298,13 +317,10 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
           T en = T(0);
           auto emit = [&](int a, const T fv[3]) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              if constexpr (GAMMA) en += fv[c] * u(a, c);
+            for (int c = 0; c < 3; ++c)
               atomicAdd(reinterpret_cast<double*>(fbase + fo[a]) + c * NR, double(fv[c]));
-            }
           };
-          T unused = T(0);
-          p2_apply<T>(Gm, cl, cm, u, emit, false, unused);
+          p2_apply<GAMMA>(Gm, cl, cm, u, emit, GAMMA, en);
           if constexpr (GAMMA) {
             if constexpr (kLaneCase) en_acc += double(en);
             else atomicAdd(&gsum[r], double(en));
@@ -346,6 +362,22 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
             us[a][c] = ld(3 + a, c);
             fd[a][c] = fs[a][c] = 0.0;
           }
+        T up[3] = {T(0), T(0), T(0)};
+        if constexpr (kShift) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            up[c] = ud[0][c];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              if (a > 0) ud[a][c] -= up[c];
+              us[a][c] -= up[c];
+            }
+          }
+        }
+        auto shift = [&](T v, int c) -> T {
+          if constexpr (kShift) return v - up[c];
+          else return v;
+        };
         const T* grow = gfan + (size_t(cf0 + c0 + f) * kFanLen) * 16;
 #pragma unroll
         for (int i = 0; i < kFanLen; ++i) {
@@ -355,8 +387,8 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) un[a][c] = ld(fan_spoke(i + 1) + a, c);
-            ur[c] = ld(fan_rim(i), c);
+            for (int a = 0; a < 3; ++a) un[a][c] = shift(ld(fan_spoke(i + 1) + a, c), c);
+            ur[c] = shift(ld(fan_rim(i), c), c);
           }
           auto u = [&](int a, int c) -> T {
             return a == 0 ? ud[0][c] : a == 1 ? ud[1][c] : a == 2 ? us[0][c] : a == 3 ? un[0][c] : a == 4 ? ud[2][c]
@@ -403,13 +435,18 @@ k_ebe_fan(const T* __restrict__ gfan, const uint32_t* __restrict__ fanw, const i
           auto emit = [&](int a, const T fv[3]) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-              if constexpr (GAMMA) en += fv[c] * u(a, c);
+              if constexpr (kShift) {
+                if (a > 0) en += fv[c] * u(a, c);
+              } else if constexpr (GAMMA) {  // (not before the forces: the differences would occupy registers)
+                if (a == 0) asm volatile("" : "+v"(ud[0][c]));
+                else en += fv[c] * (u(a, c) - ud[0][c]);
+              }
               if (a == 3 || a == 7 || a == 8) nx[a == 3 ? 0 : a - 6][c] = double(fv[c]);
               else add_force(a, c, double(fv[c]));
             }
           };
           T unused = T(0);
-          p2_apply<T>(Gm, cl, cm, u, emit, false, unused);
+          p2_apply<kShift>(Gm, cl, cm, u, emit, false, unused);
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             fs[0][c] = nx[0][c];

@@ -173,22 +173,24 @@ EBE_HD void sym_mv_acc(const T P[6], const T g[3], T out[3]) {
 //     sum_k S'_k : e_k + S' : sum_k e_k
 // (int L_k L_l dV = V (1 + delta_kl) / 20; engineering shears pair with the
 // shear stresses), so the nodal values need not be kept for it.
-template <typename T, class U, class Emit>
+// ZERO0: the values are relative to corner 0, which is zero and not asked for.
+template <bool ZERO0 = false, typename T, class U, class Emit>
 EBE_HD void p2_apply(const T G[4][3], T cl, T cm, U&& u, Emit&& emit, bool with_energy, T& energy) {
   T w[4][6];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = ZERO0 ? 1 : 0; i < 4; ++i) {
     const T ui[3] = {u(i, 0), u(i, 1), u(i, 2)};
     set_eng(w[i], ui, G[i]);
   }
   T A[6];
 #pragma unroll
-  for (int c = 0; c < 6; ++c) A[c] = (w[0][c] + w[1][c]) + (w[2][c] + w[3][c]);
+  for (int c = 0; c < 6; ++c) A[c] = (ZERO0 ? w[1][c] : w[0][c] + w[1][c]) + (w[2][c] + w[3][c]);
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
     const int k = edge_end(q, 0), m = edge_end(q, 1);
     const T ue[3] = {u(4 + q, 0), u(4 + q, 1), u(4 + q, 2)};
-    fma_eng(w[k], ue, G[m]);
+    if (ZERO0 && q == 0) set_eng(w[k], ue, G[m]);  // (edge 0 starts at corner 0)
+    else fma_eng(w[k], ue, G[m]);
     fma_eng(w[m], ue, G[k]);
   }
   // S'_k from the strain 4 w_k - A (w is overwritten by S'_k)
@@ -252,7 +254,7 @@ EBE_HD void p2_apply(const T G[4][3], T cl, T cm, U&& u, Emit&& emit, bool with_
 template <typename T>
 EBE_HD void p2_forces(const T G[4][3], T cl, T cm, const T u[10][3], T f[10][3]) {
   T unused = T(0);
-  p2_apply<T>(
+  p2_apply(
       G, cl, cm, [&](int a, int c) { return u[a][c]; },
       [&](int a, const T fa[3]) {
         f[a][0] = fa[0];
