@@ -427,8 +427,11 @@ ebe_status ebe_get_product_form(const ebe_mesh* mesh, int32_t level, ebe_dtype d
 /* Kernel variant of a form for (level, dtype, nrhs).  PIPELINED on level 1:
  * 0 = element geometry prefetched with the patch metadata and kept
  * in LDS (the default), 1 = read from the geometry cache by each work-item
- * of the element phase; on level 0 PIPELINED and COLOURED have one kernel
- * each and take every variant as 0.  GATHER and STAGED: 0 = element geometry read from
+ * of the element phase.  PIPELINED and COLOURED on level 0: 0 = by fans of
+ * tetrahedra or by single elements, whichever measured faster at this dtype,
+ * nrhs and number of patches, 1 = by single elements, each work-item reading
+ * its element's geometry from the cache, 2 = by fans (COLOURED: where the
+ * default can choose them, else as 0).  GATHER and STAGED: 0 = element geometry read from
  * the mesh's geometry cache (the default), 1 = formed at every product from
  * the four corner coordinates (fewer bytes where few cases share an
  * element).  DETERMINISTIC: 0 = shared nodes' partial sums staged and
@@ -437,7 +440,7 @@ ebe_status ebe_get_product_form(const ebe_mesh* mesh, int32_t level, ebe_dtype d
  * ASSEMBLED: the tile, cases per work-item and block slots per trip: FP32
  * 0 = 4 / 4, 1 = 2 / 4, 2 = 8 / 2; FP64 0 = 4 / 1, 1 = 2 / 2, 2 = 1 / 4
  * (cases per work-item reduced to a divisor of nrhs).  Variant 2 exists for
- * ASSEMBLED only; the other forms take it as 0.
+ * these alone; the other forms take it as 0.
  * Same result up to rounding; ebe_autotune sets it,
  * ebe_set_product_form resets it to 0; other forms ignore it. */
 ebe_status ebe_set_product_variant(ebe_mesh* mesh, int32_t level, ebe_dtype dtype, int32_t nrhs, int32_t variant);

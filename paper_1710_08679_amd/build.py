@@ -31,8 +31,9 @@ COMMON = [
 ]
 
 SOURCES = [
-    "ebe_fan_f32_a.hip", "ebe_fan_f32_b.hip", "ebe_fan_f64_a.hip", "ebe_fan_f64_b.hip",
-    "ebe_wide.hip", "ebe_kernels.hip", "ebe_pipe_f32.hip", "ebe_pipe_f64.hip", "ebe_det.hip", "setup_kernels.hip", "ebe_vec.hip",
+    "ebe_fan_f32_a.hip", "ebe_fan_f32_b.hip", "ebe_fan_f64_a.hip", "ebe_fan_f64_b.hip", "ebe_elem_f32_a.hip",
+    "ebe_elem_f32_b.hip", "ebe_elem_f64_a.hip", "ebe_elem_f64_b.hip", "ebe_wide.hip", "ebe_kernels.hip",
+    "ebe_pipe_f32.hip", "ebe_pipe_f64.hip", "ebe_det.hip", "setup_kernels.hip", "ebe_vec.hip",
     "ebe_adjoint.hip", "solver_kernels.hip", "greens_kernels.hip", "batch_kernels.hip",
     "mesh.cpp", "patches.cpp", "assembled.cpp", "api.cpp", "solver.cpp", "batch.cpp", "autotune.cpp", "greens.cpp",
 ]

@@ -50,16 +50,23 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
     // the element geometry kept in LDS or read per work-item, gather and
     // staged with the geometry read from the cache or formed from the corner
     // coordinates, deterministic with staging or colour by colour; the
-    // assembled form comes in three tiles: measure them all
+    // assembled form comes in three tiles, and the pipelined form of the
+    // quadratic level goes by the default of its size, by single elements or by
+    // fans: measure them all (coloured, which comes behind the pipelined form,
+    // only its default)
     const bool curved = order == 2 && m->curved;
-    const int nvar = form == EBE_FORM_ASSEMBLED ? 3  // tiles: cases per work-item, slots per trip
+    const int nvar = form == EBE_FORM_ASSEMBLED || (form == EBE_FORM_PIPELINED && level == 0)
+                         ? 3
                      : ((form == EBE_FORM_PIPELINED && level == 1) ||
                         ((form == EBE_FORM_GATHER || form == EBE_FORM_STAGED) && !curved) ||
                         (form == EBE_FORM_DETERMINISTIC && m->pl[0].coff.size() > 1))
                          ? 2
                          : 1;
     for (int var = 0; var < nvar && e == hipSuccess; ++var) {
+      m->fvar[lv][k][nrhs] = 0;
+      const QuadKernel usual = quad_kernel(m, form, dt, nrhs, false);
       m->fvar[lv][k][nrhs] = int8_t(var);
+      if (level == 0 && form == EBE_FORM_PIPELINED && var > 0 && quad_kernel(m, form, dt, nrhs, false) == usual) continue;
       e = launch_ebe_form(m, order, form, dt, nrhs, x, y, false, m->has_bc, false, nullptr, s);  // warm-up
       for (int r = 0; r < kRuns && e == hipSuccess; ++r) {
         e = hipEventRecord(a, s);

@@ -196,8 +196,8 @@ struct PatchLevel {
   DBuf stage;   // staging buffer [nslots][3][nrhs] of the product's dtype
   int64_t nslots = 0, nshared = 0, entries = 0;
   int max_nodes = 0;
-  // element node words [E][4] (linear level): node id | patch-local id <<
-  // kPtabLocalShift; empty on meshes of 2^25 nodes or more
+  // element node words [E][10] (quadratic, straight meshes) or [E][4] (linear): node id |
+  // patch-local id << kPtabLocalShift; empty on meshes of 2^25 nodes or more
   DBuf ptab;
   // colouring of the patches (quadratic level): no two patches of a colour
   // share a node; cperm lists the patches colour by colour (increasing id
@@ -217,6 +217,54 @@ struct PatchLevel {
 constexpr int kPtabLocalShift = 25;
 constexpr uint32_t kPtabIdMask = (1u << kPtabLocalShift) - 1;
 static_assert(kPatchNodes <= 128 && kLinPatchCorners <= 128, "patch-local ids must fit 7 bits");
+
+// Kernels of the pipelined and coloured forms on the quadratic level: by fans
+// of tetrahedra (fan_kernel.h; pipelined at up to kWideCases cases by wide
+// patches, ebe_wide.hip) or by single elements (pipe_kernel.h), the geometry
+// read per work-item or kept in LDS.
+enum class QuadKernel { fans, elements, elements_lds };
+
+// Patches of 48 elements from which fans are the faster, by [pipelined,
+// coloured, pipelined with (x, K x)][FP64, FP32][cases].  A fan's work-item is three tetrahedra long, so
+// it needs several patches per workgroup to hide that; below, one element a
+// work-item ends sooner (pipelined, 29x23x17 lattice, 1417 patches, elements / fans:
+// FP64 8 cases 32.5 / 35.5 us, 16 53.4 / 51.8; FP32 8 24.7 / 27.0, 16 33.4 / 33.8;
+// 64x64x40 lattice, 20480 patches: 478 / 376, 866 / 660; 267 / 224, 443 / 367).  At
+// FP64 5 and FP32 9 and 10 cases only the chains of larger meshes repay fans
+// (40x40x20: FP64 5 cases 59.8 / 64.2, FP32 9 82.0 / 87.8).  A colour is an eighth of
+// the mesh, and its launch ends with its slowest workgroup (coloured, 1417
+// patches: FP64 1 case 102 / 151 us, FP32 8 87 / 148, 16 115 / 153; 20480: FP32 8 285
+// / 264, 12 426 / 348, 16 424 / 396): never by fans at up to 5 cases and at most
+// numbers of cases in FP64.  (x, K x) costs each workgroup an addition to one of a
+// few places in memory, so wide patches, of which there are fewer, repay
+// themselves earlier with it (1417 patches, FP32 1 case 30.0 / 20.4 us; without
+// 12.8 / 15.8) and fans later (FP32 7 cases 34.8 / 40.9; without 31.8 / 29.5);
+// coloured it goes by elements, whose registers have room for it (6912 patches,
+// FP32 8 cases 144 against 223).  Measured on twelve lattices of 144 to 32768 patches
+// at 1 to 16 cases; each number lies between the sizes where the order changes.
+constexpr int32_t kNever = 0x7fffffff;
+constexpr int32_t kFanFrom[3][2][EBE_MAX_RHS + 1] = {
+    {{0, 5000, 1200, 3500, 3500, 6144, 2200, 1200, 2200, 1200, 1200, 1200, 1200, 1200, 2200, 0, 0},
+     {0, 5000, 3500, 5000, 2200, 2200, 1200, 1200, 2200, 6144, 6144, 2200, 1200, 3500, 1200, 3500, 2200}},
+    {{0, kNever, kNever, kNever, kNever, kNever, 6144, 32000, kNever, kNever, kNever, kNever, kNever, kNever, 3500,
+      kNever, 20000},
+     {0, kNever, kNever, kNever, kNever, kNever, 6144, 14000, 6500, kNever, kNever, 9000, 6144, 14000, 9000, 20000,
+      9000}},
+    {{0, 1200, 1200, 3500, 3500, 2200, 2200, 2200, 4500, 4500, 1200, 1200, 1200, 1200, 0, 0, 0},
+     {0, 1200, 1200, 1200, 1200, 5000, 2200, 2200, 6144, 10000, 6144, 2200, 2200, 2200, 1200, 2200, 3500}}};
+
+// Elements with the geometry in LDS are instantiated where they measured 1 to 7%
+// faster than the other two: coloured, FP64, 6 and 7 cases on smaller meshes
+// (40x40x20 lattice 104 us against 113, 135 against 143; 5952 patches 223 against
+// 231, but 290 against 251), pipelined, FP64, 9 to 11 and FP32, 9 and 10 cases on
+// meshes without chains (40x40x20: FP64 9 cases 109 against 113, 10 110 against
+// 112, FP32 10 76.2 against 77.1).
+constexpr bool lds_elements(bool colour, int value_bytes, int nr) {
+  return colour ? value_bytes == 8 && (nr == 6 || nr == 7) : (nr == 9 || nr == 10 || (value_bytes == 8 && nr == 11));
+}
+constexpr bool lds_patches(bool colour, int nr, int64_t npatch) {
+  return colour ? npatch < (nr == 6 ? 6144 : 5000) : npatch >= 2200 && npatch < 6144;
+}
 
 constexpr int kXcds = 8;  // dies of the GPU, each with an L2 of its own
 
@@ -368,6 +416,9 @@ bool form_available(int order, int form);
 // the patch colouring
 bool form_usable(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs);
 int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs);
+// the kernel that a pipelined or coloured product of the quadratic level runs in
+// its variant; gamma: with (x, K x)
+QuadKernel quad_kernel(const ebe_mesh* m, int form, ebe_dtype dt, int nrhs, bool gamma);
 // the form and its kernel variant as one key (graph keys: a replay must run the same kernels)
 inline uintptr_t product_key(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   return uintptr_t(product_form(m, order, dt, nrhs)) |
@@ -382,6 +433,7 @@ hipError_t launch_invert_blocks(const ebe_mesh* m, int level, const double* blk6
                                 float* inv32, hipStream_t s);
 hipError_t launch_expand_blocks(int64_t n, const double* blk6, double* out9, hipStream_t s);
 hipError_t launch_lame(const ebe_mesh* m, hipStream_t s);
+hipError_t launch_node_words(const ebe_mesh* m, hipStream_t s);  // pl[0].ptab
 hipError_t launch_geometry(const ebe_mesh* m, ebe_dtype dt, void* out, hipStream_t s);
 hipError_t launch_fan_geometry(const ebe_mesh* m, ebe_dtype dt, void* out, hipStream_t s);
 // K1 of the linear (corner) mesh into k1.val[0] (FP64, atomics into zeroed

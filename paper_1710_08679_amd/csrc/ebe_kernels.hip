@@ -540,14 +540,18 @@ hipError_t ebe_dispatch_p(int order, int form, const ebe_mesh* m, const void* x,
     return launch_asm_p<T, NR>(m, m->k1, fx, x, y, mask_in, bc, add, gate, s, gamma);
   }
   if (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED) {
-    if constexpr (NR <= kWideCases) {
-      if (order == 2 && form == EBE_FORM_PIPELINED) return launch_wide<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma);
+    const bool colour = form == EBE_FORM_COLOURED;
+    if (order == 1)
+      return m->fvar[1][sizeof(T) == 8 ? 0 : 1][NR] != 1
+                 ? launch_pipe<T, NR, 1, true>(m, x, y, mask_in, bc, add, gate, s, gamma, colour)
+                 : launch_pipe<T, NR, 1, false>(m, x, y, mask_in, bc, add, gate, s, gamma, colour);
+    switch (quad_kernel(m, form, sizeof(T) == 8 ? EBE_F64 : EBE_F32, NR, gamma != nullptr)) {
+      case QuadKernel::elements: return launch_pipe<T, NR, 2, false>(m, x, y, mask_in, bc, add, gate, s, gamma, colour);
+      case QuadKernel::elements_lds: return launch_pipe_lds<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma, colour);
+      default:
+        if constexpr (NR <= kWideCases) return launch_wide<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma);
+        else return launch_fan<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma, colour);
     }
-    if (order == 2)
-      return launch_fan<T, NR>(m, x, y, mask_in, bc, add, gate, s, gamma, form == EBE_FORM_COLOURED);
-    return m->fvar[1][sizeof(T) == 8 ? 0 : 1][NR] != 1
-               ? launch_pipe<T, NR, true>(m, x, y, mask_in, bc, add, gate, s, gamma)
-               : launch_pipe<T, NR, false>(m, x, y, mask_in, bc, add, gate, s, gamma);
   }
   // stream the staged partials past the caches when they cannot stay in the
   // last-level cache until the shared-node pass reads them back
@@ -701,6 +705,25 @@ bool form_usable(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs)
   return form != EBE_FORM_COLOURED || L.coff.size() > 1;
 }
 
+namespace {
+// the mesh is one wide patch, which has no shared nodes: its products at one or
+// two cases take one launch
+bool one_wide_patch(const ebe_mesh* m, ebe_dtype dt, int nrhs) {
+  return nrhs <= 2 && m->nfan > 0 && m->wide[wide_size(dt == EBE_F64 ? 8 : 4, nrhs)].pl.nshared == 0;
+}
+}  // namespace
+
+QuadKernel quad_kernel(const ebe_mesh* m, int form, ebe_dtype dt, int nrhs, bool gamma) {
+  const int k = dt == EBE_F64 ? 0 : 1, var = m->fvar[0][k][nrhs];
+  const bool colour = form == EBE_FORM_COLOURED;
+  const int32_t from = colour ? (gamma ? kNever : kFanFrom[1][k][nrhs]) : kFanFrom[gamma ? 2 : 0][k][nrhs];
+  const int64_t n = m->pl[0].npatch;
+  if (var == 1) return QuadKernel::elements;
+  if (var == 2 && from != kNever) return QuadKernel::fans;
+  if (lds_elements(colour, k == 0 ? 8 : 4, nrhs) && lds_patches(colour, nrhs, n)) return QuadKernel::elements_lds;
+  return n >= from || (!colour && !gamma && one_wide_patch(m, dt, nrhs)) ? QuadKernel::fans : QuadKernel::elements;
+}
+
 int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   const int f = m->form[order == 2 ? 0 : 1][dt == EBE_F64 ? 0 : 1][nrhs];
   if (form_usable(m, order, f, dt, nrhs)) return f;
@@ -716,8 +739,7 @@ int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   // A mesh that is one wide patch has no shared nodes and so one launch instead
   // of two: 4^3 cube, 1 case FP64 12.4 / 10.2 us, FP32 11.9 / 10.2, 2 cases 12.8 /
   // 9.9 and 12.7 / 10.3 (3 and 4 cases: 12.8 / 16.8 and 13.1 / 14.0).
-  const bool one = nrhs <= 2 && m->nfan > 0 && m->wide[wide_size(dt == EBE_F64 ? 8 : 4, nrhs)].pl.nshared == 0;
-  if (order == 2 && (one || m->pl[0].npatch >= from) && form_usable(m, 2, EBE_FORM_PIPELINED, dt, nrhs))
+  if (order == 2 && (one_wide_patch(m, dt, nrhs) || m->pl[0].npatch >= from) && form_usable(m, 2, EBE_FORM_PIPELINED, dt, nrhs))
     return EBE_FORM_PIPELINED;
   return EBE_FORM_GATHER;
 }
@@ -731,7 +753,9 @@ hipError_t launch_ebe_form(const ebe_mesh* m, int order, int form, ebe_dtype dt,
   if ((staged && L.stage.bytes() < need) || L.npatch < 1 || nrhs < 1 || nrhs > EBE_MAX_RHS ||
       !form_usable(m, order, form, dt, nrhs) ||
       ((form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED || form == EBE_FORM_DETERMINISTIC) &&
-       !(order == 2 && form != EBE_FORM_DETERMINISTIC ? m->gfan_ready[k] : m->geo_ready[k])) ||
+       !(order == 2 && form != EBE_FORM_DETERMINISTIC && quad_kernel(m, form, dt, nrhs, gamma != nullptr) == QuadKernel::fans
+             ? m->gfan_ready[k]
+             : m->geo_ready[k])) ||
       (form == EBE_FORM_ASSEMBLED && !m->k1.ready[k]))
     return hipErrorInvalidValue;  // staging, geometry or assembled values not prepared, or bad form: host bug
   if (form == EBE_FORM_DETERMINISTIC)

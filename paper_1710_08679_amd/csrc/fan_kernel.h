@@ -1,5 +1,6 @@
 // Pipelined and coloured forms of the quadratic EBE product (Section 2,
-// Eq. (3)) on straight-sided elements.
+// Eq. (3)) on straight-sided elements, at more than kWideCases cases on meshes
+// of enough patches (kFanFrom).
 //
 // Fans.  The tetrahedra of a patch are grouped on the host into fans: chains
 // of at most three tetrahedra around a common edge (the spine p-q), each
@@ -100,7 +101,7 @@ __device__ __forceinline__ double row_value(double v) {
 }
 
 // GAMMA: also form gamma[r] += (x_r, K x_r), what CG needs from q = K p (never
-// with add), free of the rounding that a translation common to a tetrahedron's
+// with add, nor coloured), free of the rounding that a translation common to a tetrahedron's
 // nodes would bring in: from the nodes' differences from corner p (in FP32 the
 // error of the plain sum of force times nodal value was twice to eight times
 // that of the gather form's strains).  By tetrahedra: strains and stresses of the
@@ -594,7 +595,12 @@ hipError_t launch_fan_c(const ebe_mesh* m, const int32_t* plist, int64_t npatch,
   if (mask_in)
     return launch_fan_k<T, NR, true, false, COLOUR>(m, plist, npatch, x, y, stream, bc, add, gate, s, nullptr);
   if (gamma && add) return hipErrorInvalidValue;
-  if (gamma) return launch_fan_k<T, NR, false, true, COLOUR>(m, plist, npatch, x, y, stream, bc, add, gate, s, gamma);
+  if constexpr (COLOUR) {
+    if (gamma) return hipErrorInvalidValue;  // quad_kernel names another
+  } else {
+    if (gamma)
+      return launch_fan_k<T, NR, false, true, COLOUR>(m, plist, npatch, x, y, stream, bc, add, gate, s, gamma);
+  }
   return launch_fan_k<T, NR, false, false, COLOUR>(m, plist, npatch, x, y, stream, bc, add, gate, s, nullptr);
 }
 
@@ -604,31 +610,31 @@ template <typename T, int NR>
 hipError_t launch_fan(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add, const int* gate,
                       hipStream_t s, double* gamma, bool colour) {
   if (colour) {
-    const PatchLevel& L = m->pl[0];
-    const int32_t* cp = L.cperm.as<int32_t>();
-    for (size_t c = 0; c + 1 < L.coff.size(); ++c) {
-      const hipError_t e = launch_fan_c<T, NR, true>(m, cp + L.coff[c], L.coff[c + 1] - L.coff[c], x, y, false,
-                                                     mask_in, bc, add, gate, s, gamma);
-      if (e != hipSuccess) return e;
+    if constexpr (kFanFrom[1][sizeof(T) == 8 ? 0 : 1][NR] != kNever) {
+      const PatchLevel& L = m->pl[0];
+      const int32_t* cp = L.cperm.as<int32_t>();
+      for (size_t c = 0; c + 1 < L.coff.size(); ++c) {
+        const hipError_t e = launch_fan_c<T, NR, true>(m, cp + L.coff[c], L.coff[c + 1] - L.coff[c], x, y, false,
+                                                       mask_in, bc, add, gate, s, gamma);
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
+    } else {
+      return hipErrorInvalidValue;  // quad_kernel names another
     }
-    return hipSuccess;
   }
-  if constexpr (NR > kWideCases) {
-    // stream the staged partials past the caches when they cannot stay in the
-    // last-level cache until the shared-node pass reads them back
-    const PatchLevel& L = m->chain;
-    const bool st = int64_t(L.nslots) * 3 * NR * int64_t(sizeof(T)) > kStreamStageBytes;
-    hipError_t e = launch_fan_c<T, NR, false>(m, m->cseq.as<int32_t>(), L.npatch, x, y, st, mask_in, bc, add, gate, s,
-                                              gamma);
-    if (e != hipSuccess || L.nshared == 0) return e;
-    const int64_t work = L.nshared * (3 * NR / reduce_width<T, NR>());
-    hipLaunchKernelGGL((k_reduce_shared<T, NR>), dim3(unsigned((work + 255) / 256)), dim3(256), 0, s,
-                       L.snode.as<int32_t>(), L.soff.as<int32_t>(), m->pl[0].stage.as<T>(), int(st), static_cast<T*>(y),
-                       int32_t(L.nshared), int(bc), int(add), gate);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;  // the wide patches' kernel takes these
-  }
+  // stream the staged partials past the caches when they cannot stay in the
+  // last-level cache until the shared-node pass reads them back
+  const PatchLevel& L = m->chain;
+  const bool st = int64_t(L.nslots) * 3 * NR * int64_t(sizeof(T)) > kStreamStageBytes;
+  hipError_t e = launch_fan_c<T, NR, false>(m, m->cseq.as<int32_t>(), L.npatch, x, y, st, mask_in, bc, add, gate, s,
+                                            gamma);
+  if (e != hipSuccess || L.nshared == 0) return e;
+  const int64_t work = L.nshared * (3 * NR / reduce_width<T, NR>());
+  hipLaunchKernelGGL((k_reduce_shared<T, NR>), dim3(unsigned((work + 255) / 256)), dim3(256), 0, s,
+                     L.snode.as<int32_t>(), L.soff.as<int32_t>(), m->pl[0].stage.as<T>(), int(st), static_cast<T*>(y),
+                     int32_t(L.nshared), int(bc), int(add), gate);
+  return hipGetLastError();
 }
 
 }  // namespace ebe

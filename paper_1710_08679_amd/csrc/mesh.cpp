@@ -374,9 +374,11 @@ static ebe_status create_mesh(const char* fn, bool curved, const double* xyz, in
   if (st == EBE_OK) st = build_patches(m, conn10, fix.data(), up);
   if (st == EBE_OK) st = up.finish(m->small_tables);
   if (st == EBE_OK) st = m->gacc.alloc(kGammaBytes);
+  if (st == EBE_OK && m->nfan > 0) st = m->pl[0].ptab.alloc(size_t(E) * 10 * sizeof(uint32_t));
   if (st == EBE_OK) {
     hipError_t he = launch_lame(m, s);
     if (he == hipSuccess) he = launch_fill_zero(m->gacc.as<void>(), kGammaBytes, s);
+    if (he == hipSuccess && m->nfan > 0) he = launch_node_words(m, s);
     if (he == hipSuccess) he = hipStreamSynchronize(s);
     if (he != hipSuccess) {
       set_error("%s: upload failed: %s", fn, hipGetErrorString(he));

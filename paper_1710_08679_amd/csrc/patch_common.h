@@ -254,13 +254,18 @@ __global__ __launch_bounds__(256) void k_reduce_shared(const int32_t* __restrict
 
 }  // namespace
 
-// Pipelined form of the linear product (pipe_kernel.h) and pipelined and
-// coloured forms of the quadratic one (fan_kernel.h), instantiated in
-// ebe_pipe_*.hip and ebe_fan_*.hip.  GEO: element geometry kept in LDS (else
-// read per work-item).  The caller checks form_usable() first.
-template <typename T, int NR, bool GEO>
+// Pipelined and coloured (quadratic level) forms by single elements
+// (pipe_kernel.h) and, on the quadratic level, by fans (fan_kernel.h),
+// instantiated in ebe_pipe_*.hip, ebe_elem_*.hip and ebe_fan_*.hip.  GEO:
+// element geometry kept in LDS (else read per work-item).  The caller checks
+// form_usable() first and asks quad_kernel().
+template <typename T, int NR, int ORDER, bool GEO>
 hipError_t launch_pipe(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add, const int* gate,
-                       hipStream_t s, double* gamma);
+                       hipStream_t s, double* gamma, bool colour);
+// the same of the quadratic level with the geometry in LDS, where lds_elements()
+template <typename T, int NR>
+hipError_t launch_pipe_lds(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add,
+                           const int* gate, hipStream_t s, double* gamma, bool colour);
 template <typename T, int NR>
 hipError_t launch_fan(const ebe_mesh* m, const void* x, void* y, bool mask_in, bool bc, bool add, const int* gate,
                       hipStream_t s, double* gamma, bool colour);

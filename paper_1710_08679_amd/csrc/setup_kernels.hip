@@ -207,6 +207,17 @@ __global__ __launch_bounds__(kBlock) void k_lame(const double* __restrict__ E,
   l32[i] = make_float2(float(lam), float(mu));
 }
 
+// Element node words of the quadratic level from its two tables (formed here:
+// an upload of them would be a third of the mesh's).
+__global__ __launch_bounds__(kBlock) void k_node_words(const int32_t* __restrict__ conn,
+                                                       const uint8_t* __restrict__ lconn, uint32_t* __restrict__ ptab,
+                                                       int64_t n) {
+  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const int64_t e = i / 10;
+  ptab[i] = (uint32_t(conn[i]) & kPtabIdMask) | (uint32_t(lconn[e * 16 + (i - e * 10)]) << kPtabLocalShift);
+}
+
 // a geometry row of 16 values, in 16-byte stores
 template <typename T>
 __device__ __forceinline__ void store_row(T* __restrict__ out, const T o[16]) {
@@ -616,6 +627,13 @@ hipError_t launch_expand_blocks(int64_t n, const double* blk6, double* out9, hip
 hipError_t launch_lame(const ebe_mesh* m, hipStream_t s) {
   hipLaunchKernelGGL(k_lame, dim3(grid_for(m->n_elem)), dim3(kBlock), 0, s, m->young.as<double>(),
                      m->poisson.as<double>(), m->lame64.as<double2>(), m->lame32.as<float2>(), m->n_elem);
+  return hipGetLastError();
+}
+
+hipError_t launch_node_words(const ebe_mesh* m, hipStream_t s) {
+  const int64_t n = m->n_elem * 10;
+  hipLaunchKernelGGL(k_node_words, dim3(grid_for(n)), dim3(kBlock), 0, s, m->conn.as<int32_t>(),
+                     m->lconn.as<uint8_t>(), m->pl[0].ptab.as<uint32_t>(), n);
   return hipGetLastError();
 }
 

@@ -23,6 +23,7 @@ pytestmark = pytest.mark.gpu
 
 DT = {np.float64: torch.float64, np.float32: torch.float32}
 FORMS = [(ebe.FORM_GATHER, 0), (ebe.FORM_STAGED, 0), (ebe.FORM_PIPELINED, 0), (ebe.FORM_PIPELINED, 1),
+         (ebe.FORM_PIPELINED, 2), (ebe.FORM_COLOURED, 2),
          (ebe.FORM_COLOURED, 0), (ebe.FORM_COLOURED, 1)]
 
 
