@@ -419,7 +419,10 @@ ebe_status ebe_autotune(ebe_mesh* mesh, int32_t level, ebe_dtype dtype, int32_t 
 /* Force (EBE_FORM_GATHER / _STAGED / _PIPELINED, _COLOURED and
  * _DETERMINISTIC for level 0, _ASSEMBLED for level 1) or reset
  * (EBE_FORM_AUTO) the form used
- * for (level, dtype, nrhs), and read the form that would be used. */
+ * for (level, dtype, nrhs), and read the form that would be used.  On a mesh
+ * that has had products of this dtype, setting a form (or a variant, below)
+ * also allocates and fills the element geometry that it reads and they did
+ * not, so that its next product can be captured into a graph. */
 ebe_status ebe_set_product_form(ebe_mesh* mesh, int32_t level, ebe_dtype dtype, int32_t nrhs, int32_t form);
 ebe_status ebe_get_product_form(const ebe_mesh* mesh, int32_t level, ebe_dtype dtype, int32_t nrhs,
                                 int32_t* form);

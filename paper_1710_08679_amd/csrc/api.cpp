@@ -139,15 +139,98 @@ ebe_status ensure_half(ebe_mesh* m, int level, hipStream_t s) {
   return EBE_OK;
 }
 
-ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s) {
-  ebe_status st = ensure_stage(m, nrhs, dt == EBE_F64 ? 8 : 4);
+GeometryNeed geometry_need(const ebe_mesh* m, int level, int form, ebe_dtype dt, int nrhs, bool gamma) {
+  GeometryNeed n;
+  if (level == 0 && m->curved) return n;  // formed in the kernel
+  if (form == EBE_FORM_GATHER || form == EBE_FORM_STAGED)
+    n.elements = m->fvar[level][dt == EBE_F64 ? 0 : 1][nrhs] != 1;
+  else if (level == 0 && (form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED)) {
+    if (quad_kernel(m, form, dt, nrhs, gamma) == QuadKernel::fans) n.fans = nrhs > kWideCases;
+    else n.elements = true;
+  } else {
+    n.elements = form != EBE_FORM_ASSEMBLED;
+  }
+  return n;
+}
+
+namespace {
+
+GeometryNeed need_now(const ebe_mesh* m, int level, ebe_dtype dt, int nrhs, bool gamma) {
   const int form = product_form(m, level == 0 ? 2 : 1, dt, nrhs);
-  // (both geometry caches, whichever the form reads: after one product another
-  // form can be set and captured into a graph without an allocation)
-  if (st == EBE_OK) st = ensure_geometry(m, dt, s);
-  if (st == EBE_OK && level == 0) st = ensure_fan_geometry(m, dt, s);
-  if (st == EBE_OK && level == 1 && form == EBE_FORM_ASSEMBLED) st = ensure_assembled(m, dt, s);
+  GeometryNeed n = geometry_need(m, level, form, dt, nrhs, false);
+  if (gamma) {
+    const GeometryNeed g = geometry_need(m, level, form, dt, nrhs, true);
+    n.elements |= g.elements;
+    n.fans |= g.fans;
+  }
+  return n;
+}
+
+// Whether a first use of a cache must go without it: nothing can be allocated
+// while a stream is being captured (launch_ebe_form then takes a kernel that
+// forms the geometry itself).
+bool must_skip(const DBuf& b, hipStream_t s) {
+  if (b.bytes() > 0) return false;
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // (the legacy stream while another is being captured)
+  return true;
+}
+
+}  // namespace
+
+ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s, bool gamma) {
+  const int k = dt == EBE_F64 ? 0 : 1;
+  ebe_status st = ensure_stage(m, nrhs, dt == EBE_F64 ? 8 : 4);
+  if (st != EBE_OK) return st;
+  const GeometryNeed n = need_now(m, level, dt, nrhs, gamma);
+  m->prepared[k] = true;
+  m->geo_used[k] |= n.elements;
+  m->gfan_used[k] |= n.fans;
+  if (m->geo_used[k] && !m->geo_ready[k] && !must_skip(m->geo[k], s)) st = ensure_geometry(m, dt, s);
+  if (st == EBE_OK && m->gfan_used[k] && !m->gfan_ready[k] && !must_skip(m->gfan[k], s))
+    st = ensure_fan_geometry(m, dt, s);
+  if (st == EBE_OK && level == 1 && product_form(m, 1, dt, nrhs) == EBE_FORM_ASSEMBLED)
+    st = ensure_assembled(m, dt, s);
   return st;
+}
+
+void prepare_chosen_form(ebe_mesh* m, int level, ebe_dtype dt, int nrhs) {
+  const int k = dt == EBE_F64 ? 0 : 1;
+  if (!m->prepared[k]) return;  // the first product prepares what it needs
+  const GeometryNeed n = need_now(m, level, dt, nrhs, true);
+  // (a cache that products have read already is theirs to fill again, on their stream)
+  const bool elements = n.elements && m->geo[k].bytes() == 0, fans = n.fans && m->gfan[k].bytes() == 0;
+  if (!elements && !fans) return;
+  // on a stream of its own, also while this thread or another captures one
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+  int prev = 0;
+  hipStream_t s = nullptr;
+  hipError_t e = hipGetDevice(&prev);
+  if (e == hipSuccess) e = hipSetDevice(m->device);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e == hipSuccess && m->material) e = hipStreamWaitEvent(s, m->material, 0);
+  bool ok = e == hipSuccess;
+  if (ok && elements) ok = ensure_geometry(m, dt, s) == EBE_OK;
+  if (ok && fans) ok = ensure_fan_geometry(m, dt, s) == EBE_OK;
+  if (s) {
+    if (hipStreamSynchronize(s) != hipSuccess) ok = false;
+    (void)hipStreamDestroy(s);
+  }
+  if (!ok) {
+    if (elements) {
+      m->geo_ready[k] = false;
+      m->geo[k].release();
+    }
+    if (fans) {
+      m->gfan_ready[k] = false;
+      m->gfan[k].release();
+    }
+    (void)hipGetLastError();
+  }
+  (void)hipSetDevice(prev);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
 }
 
 // Form and invert the 3x3 block-Jacobi blocks of both levels (once per material).

@@ -33,8 +33,8 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
                         double ms[EBE_NUM_FORMS]) {
   const int order = level == 0 ? 2 : 1;
   ebe_status st = ensure_stage(m, nrhs, dt == EBE_F64 ? 8 : 4);
-  if (st == EBE_OK) st = ensure_geometry(m, dt, s);
-  if (st == EBE_OK && level == 0) st = ensure_fan_geometry(m, dt, s);
+  if (st == EBE_OK && (level == 1 || !m->curved)) st = ensure_geometry(m, dt, s);
+  if (st == EBE_OK && level == 0 && nrhs > kWideCases) st = ensure_fan_geometry(m, dt, s);
   if (st == EBE_OK && level == 1) st = ensure_assembled(m, dt, s);
   if (st != EBE_OK) return st;
   hipEvent_t a = nullptr, b = nullptr;
@@ -129,6 +129,7 @@ ebe_status ebe_set_product_form(ebe_mesh* m, int32_t level, ebe_dtype dt, int32_
   }
   m->form[level][dt == EBE_F64 ? 0 : 1][nrhs] = int8_t(form);
   m->fvar[level][dt == EBE_F64 ? 0 : 1][nrhs] = 0;
+  prepare_chosen_form(m, level, dt, nrhs);
   return EBE_OK;
 }
 
@@ -139,6 +140,7 @@ ebe_status ebe_set_product_variant(ebe_mesh* m, int32_t level, ebe_dtype dt, int
     return EBE_ERR_ARG;
   }
   m->fvar[level][dt == EBE_F64 ? 0 : 1][nrhs] = int8_t(variant);
+  prepare_chosen_form(m, level, dt, nrhs);
   return EBE_OK;
 }
 

@@ -348,6 +348,10 @@ struct ebe_mesh {
   // lambda V / 20 at 3, mu V / 20 at 7), for the pipelined and coloured forms of the quadratic level
   ebe::DBuf gfan[2];
   bool gfan_ready[2] = {false, false};
+  // by dtype: a product has been prepared; it read geo, gfan (filled again after
+  // a change of material whichever form is next: captured graphs may read them)
+  bool prepared[2] = {false, false}, geo_used[2] = {false, false}, gfan_used[2] = {false, false};
+  hipEvent_t material = nullptr;  // recorded when a change of material has been enqueued
   // assembled linear-level operator K1 over the corner graph (its edges are
   // the quadratic mesh's edge nodes); structure at creation, values on demand
   ebe::AsmOp k1;
@@ -465,16 +469,30 @@ hipError_t launch_adjoint(const ebe_mesh* m, ebe_dtype dt, int nrhs, const void*
                           const void* lam, void* g, hipStream_t s);
 
 ebe_status ensure_blocks(ebe_mesh* m, hipStream_t s);
-// fill the geometry cache of dtype dt if needed (allocates: call before any
-// graph capture; every entry point that launches products does)
+// the geometry caches that products of (level, dtype, nrhs) read in their form
+// and variant (gamma: with (x, K x)): geo, gfan
+struct GeometryNeed {
+  bool elements = false, fans = false;
+};
+GeometryNeed geometry_need(const ebe_mesh* m, int level, int form, ebe_dtype dt, int nrhs, bool gamma);
+inline bool geometry_ready(const ebe_mesh* m, GeometryNeed n, ebe_dtype dt) {
+  const int k = dt == EBE_F64 ? 0 : 1;
+  return (!n.elements || m->geo_ready[k]) && (!n.fans || m->gfan_ready[k]);
+}
+// fill the geometry cache of dtype dt if it is not (allocates the first time)
 ebe_status ensure_geometry(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
 // the same for the fan-ordered rows
 ebe_status ensure_fan_geometry(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
+// A form or variant was chosen after products of this dtype: allocate and fill
+// the cache that it reads now, so that its first product can be captured.  (Not
+// an error when it cannot be: the product tries again.)
+void prepare_chosen_form(ebe_mesh* m, int level, ebe_dtype dt, int nrhs);
 // build the assembled linear-level operator of dtype dt if needed (allocates)
 ebe_status ensure_assembled(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
 // everything products of (level, dtype, nrhs) in their current form need:
-// staging, geometry cache, assembled operator (allocates: before any capture)
-ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s);
+// staging, the geometry cache that it reads, assembled operator (allocates:
+// before any capture); gamma: also products with (x, K x)
+ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s, bool gamma = false);
 ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix, Uploads& s);
 // ---- assembled operators (assembled.cpp) ------------------------------------
 // CSR rows (each increasing, non-empty) -> sliced layout with the columns' fix bits

@@ -747,19 +747,21 @@ int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
 hipError_t launch_ebe_form(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs, const void* x, void* y,
                            bool mask_in, bool bc, bool add, const int* gate, hipStream_t s, double* gamma) {
   const PatchLevel& L = m->pl[order == 2 ? 0 : 1];
+  const int level = order == 2 ? 0 : 1;
+  // a captured product whose form's cache could not be allocated (prepare_products)
+  if ((form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED) && nrhs >= 1 && nrhs <= EBE_MAX_RHS &&
+      form_usable(m, order, form, dt, nrhs) &&
+      !geometry_ready(m, geometry_need(m, level, form, dt, nrhs, gamma != nullptr), dt))
+    form = EBE_FORM_GATHER;
   const size_t need = size_t(L.nslots) * 3 * size_t(nrhs) * (dt == EBE_F64 ? 8 : 4);
   const int k = dt == EBE_F64 ? 0 : 1;
   const bool staged = form != EBE_FORM_COLOURED && form != EBE_FORM_ASSEMBLED;
   if ((staged && L.stage.bytes() < need) || L.npatch < 1 || nrhs < 1 || nrhs > EBE_MAX_RHS ||
       !form_usable(m, order, form, dt, nrhs) ||
-      ((form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED || form == EBE_FORM_DETERMINISTIC) &&
-       !(order == 2 && form != EBE_FORM_DETERMINISTIC && quad_kernel(m, form, dt, nrhs, gamma != nullptr) == QuadKernel::fans
-             ? m->gfan_ready[k]
-             : m->geo_ready[k])) ||
-      (form == EBE_FORM_ASSEMBLED && !m->k1.ready[k]))
+      (form == EBE_FORM_DETERMINISTIC && !m->geo_ready[k]) || (form == EBE_FORM_ASSEMBLED && !m->k1.ready[k]))
     return hipErrorInvalidValue;  // staging, geometry or assembled values not prepared, or bad form: host bug
   if (form == EBE_FORM_DETERMINISTIC)
-    return launch_det(m, dt, nrhs, m->fvar[order == 2 ? 0 : 1][k][nrhs] == 1 && L.coff.size() > 1, x, y, mask_in, bc,
+    return launch_det(m, dt, nrhs, m->fvar[level][k][nrhs] == 1 && L.coff.size() > 1, x, y, mask_in, bc,
                       add, gate, s, gamma);
   return dt == EBE_F64 ? ebe_dispatch<double>(order, form, m, nrhs, x, y, mask_in, bc, add, gate, s, gamma)
                        : ebe_dispatch<float>(order, form, m, nrhs, x, y, mask_in, bc, add, gate, s, gamma);

@@ -434,6 +434,8 @@ ebe_status ebe_mesh_set_material(ebe_mesh* m, const double* young_dev, const dou
   m->gfan_ready[0] = m->gfan_ready[1] = false;
   m->k1.ready[0] = m->k1.ready[1] = m->k1.ready16 = false;
   m->a2.ready[0] = m->a2.ready[1] = m->a2.ready16 = false;
+  if (!m->material) EBE_TRY_HIP(hipEventCreateWithFlags(&m->material, hipEventDisableTiming));
+  EBE_TRY_HIP(hipEventRecord(m->material, s));
   return EBE_OK;
 }
 
@@ -452,6 +454,7 @@ void ebe_mesh_destroy(ebe_mesh* m) {
   if (!m) return;
   if (m->ws.host_flags) (void)hipHostFree(m->ws.host_flags);
   for (auto& g : m->ws.graphs) (void)hipGraphExecDestroy(g.exec);
+  if (m->material) (void)hipEventDestroy(m->material);
   delete m;
 }
 

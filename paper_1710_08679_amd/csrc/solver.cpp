@@ -318,8 +318,6 @@ ebe_status ebe_pcg_solve(ebe_mesh* m, int32_t nr, const double* f, double* u, co
   if ((st_ = ensure_blocks(m, s)) != EBE_OK) return st_;
   if ((st_ = ensure_stage(m, nr, sizeof(double))) != EBE_OK) return st_;
   if ((st_ = ensure_workspace(m, nr)) != EBE_OK) return st_;
-  if ((st_ = ensure_geometry(m, EBE_F64, s)) != EBE_OK) return st_;
-  if (o.mode == EBE_MODE_MIXED && (st_ = ensure_geometry(m, EBE_F32, s)) != EBE_OK) return st_;
 
   Workspace& w = m->ws;
   SolverState st;
@@ -351,8 +349,12 @@ ebe_status ebe_pcg_solve(ebe_mesh* m, int32_t nr, const double* f, double* u, co
     double ms[EBE_NUM_FORMS];
     if ((st_ = tune_product(m, k.level, k.dt, nr, k.x, k.y, s, ms)) != EBE_OK) return st_;
   }
-  for (int t = 0; t < (mg ? 3 : 1); ++t)
-    if ((st_ = prepare_products(m, tunes[t].level, tunes[t].dt, nr, s)) != EBE_OK) return st_;
+  if (det) {  // the deterministic form on the quadratic level, the assembled one below it
+    if ((st_ = ensure_geometry(m, EBE_F64, s)) != EBE_OK) return st_;
+    if (mg && (st_ = ensure_geometry(m, inner_dt, s)) != EBE_OK) return st_;
+  }
+  for (int t = 0; t < (mg ? 3 : 1) && !det; ++t)
+    if ((st_ = prepare_products(m, tunes[t].level, tunes[t].dt, nr, s, true)) != EBE_OK) return st_;
   if (det && mg && (st_ = ensure_assembled(m, inner_dt, s)) != EBE_OK) return st_;
   if (o.precond == EBE_PREC_MG3 && (st_ = ensure_level2(m, inner_dt, s)) != EBE_OK) return st_;
   if (o.coarse_half && o.mode != EBE_MODE_MIXED) o.coarse_half = 0;  // FP16 coarse operators feed FP32 loops only
