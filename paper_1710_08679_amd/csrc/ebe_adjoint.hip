@@ -13,7 +13,7 @@
 // Consecutive fans (which share nodes) stay on one XCD.  The kernel waits for
 // its loads (bytes at 64x64x32 hexahedra x 6, FP64, 4 cases: 0.26 GB); one
 // work-item per (element, case) with the elements dealt to the XCDs in turn
-// took 240 us there.  The element-by-element kernel below serves meshes
+// took 240 us there.  The element-by-element kernels below serve meshes
 // without fans (2^25 nodes or more).
 #include <hip/hip_runtime.h>
 
@@ -137,7 +137,50 @@ void launch_adjoint_fan(const ebe_mesh* m, const typename Pair<T>::type* lame, c
                      lame, u, lam, g, m->nfan);
 }
 
-// one work-item per element, looping over the cases
+// one work-item per (element, case), NR a power of two: an element's cases are
+// adjacent lanes of one wavefront
+template <typename T, int NR>
+__global__ __launch_bounds__(kBlock) void k_adjoint(const int32_t* __restrict__ conn, const double4* __restrict__ xv,
+                                                    const double* __restrict__ young,
+                                                    const typename Pair<T>::type* __restrict__ lame,
+                                                    const T* __restrict__ u, const T* __restrict__ lam,
+                                                    T* __restrict__ g, int64_t nelem) {
+  const int64_t t = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const int64_t e = t / NR;
+  const int r = int(t - e * NR);
+  const bool live = e < nelem;
+  T acc = T(0);
+  if (live) {
+    int32_t cw[10];
+#pragma unroll
+    for (int a = 0; a < 10; ++a) cw[a] = conn[e * 10 + a];
+    T G[4][3];
+    const T V = tet_geometry<T>(xv[cw[0] & kIdxMask], xv[cw[1] & kIdxMask], xv[cw[2] & kIdxMask],
+                                xv[cw[3] & kIdxMask], G);
+    const auto lm = lame[e];
+    const T s = V * T(0.05) / T(young[e]);
+    // nodal values read as needed, each nodal force contracted with the
+    // adjoint state as soon as it is known
+    T unused = T(0);
+    p2_apply(
+        G, T(lm.x) * s, T(lm.y) * s,
+        [&](int a, int c) -> T {
+          return ((cw[a] >> (kIdxBits + c)) & 1) ? T(0) : u[size_t(cw[a] & kIdxMask) * (3 * NR) + c * NR + r];
+        },
+        [&](int a, const T f[3]) {
+          const T* p = lam + size_t(cw[a] & kIdxMask) * (3 * NR) + r;
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            if (!((cw[a] >> (kIdxBits + c)) & 1)) acc += p[c * NR] * f[c];
+        },
+        false, unused);
+  }
+#pragma unroll
+  for (int off = 1; off < NR; off <<= 1) acc += __shfl_xor(acc, off, NR);
+  if (live && r == 0) g[e] = -acc;
+}
+
+// other numbers of cases: one work-item per element, looping over them
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_adjoint_loop(const int32_t* __restrict__ conn,
                                                          const double4* __restrict__ xv,
@@ -175,19 +218,34 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_loop(const int32_t* __restri
 }
 
 template <typename T>
-hipError_t adjoint_t(const ebe_mesh* m, int nrhs, const void* u, const void* lam, void* g, hipStream_t s) {
+hipError_t adjoint_elements_t(const ebe_mesh* m, int nrhs, const typename Pair<T>::type* lame, const T* u,
+                              const T* lam, T* g, hipStream_t s) {
+  auto grid = [](int64_t work) { return dim3(unsigned((work + kBlock - 1) / kBlock)); };
+  switch (nrhs) {
+#define EBE_CASE(n)                                                                                             \
+  case n:                                                                                                       \
+    hipLaunchKernelGGL((k_adjoint<T, n>), grid(m->n_elem * n), dim3(kBlock), 0, s, m->conn.as<int32_t>(),       \
+                       m->xv.as<double4>(), m->young.as<double>(), lame, u, lam, g, m->n_elem);                 \
+    break;
+    EBE_CASE(1) EBE_CASE(2) EBE_CASE(4) EBE_CASE(8) EBE_CASE(16)
+#undef EBE_CASE
+    default:
+      hipLaunchKernelGGL(k_adjoint_loop<T>, grid(m->n_elem), dim3(kBlock), 0, s, m->conn.as<int32_t>(),
+                         m->xv.as<double4>(), m->young.as<double>(), lame, u, lam, g, m->n_elem, nrhs);
+  }
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t adjoint_t(const ebe_mesh* m, int nrhs, const void* u, const void* lam, void* g, hipStream_t s,
+                     bool by_element) {
   using P = typename Pair<T>::type;
   const T* uu = static_cast<const T*>(u);
   const T* ll = static_cast<const T*>(lam);
   T* gg = static_cast<T*>(g);
   const P* lame = (sizeof(T) == 8) ? reinterpret_cast<const P*>(m->lame64.as<void>())
                                    : reinterpret_cast<const P*>(m->lame32.as<void>());
-  if (m->nfan == 0) {
-    hipLaunchKernelGGL(k_adjoint_loop<T>, dim3(unsigned((m->n_elem + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       m->conn.as<int32_t>(), m->xv.as<double4>(), m->young.as<double>(), lame, uu, ll, gg,
-                       m->n_elem, nrhs);
-    return hipGetLastError();
-  }
+  if (by_element) return adjoint_elements_t<T>(m, nrhs, lame, uu, ll, gg, s);
   switch (nrhs) {
 #define EBE_CASE(n) \
   case n: launch_adjoint_fan<T, n>(m, lame, uu, ll, gg, s); break;
@@ -202,8 +260,10 @@ hipError_t adjoint_t(const ebe_mesh* m, int nrhs, const void* u, const void* lam
 }  // namespace
 
 hipError_t launch_adjoint(const ebe_mesh* m, ebe_dtype dt, int nrhs, const void* u, const void* lam,
-                          void* g, hipStream_t s) {
-  return dt == EBE_F64 ? adjoint_t<double>(m, nrhs, u, lam, g, s) : adjoint_t<float>(m, nrhs, u, lam, g, s);
+                          void* g, hipStream_t s, bool by_element) {
+  by_element |= m->nfan == 0;
+  return dt == EBE_F64 ? adjoint_t<double>(m, nrhs, u, lam, g, s, by_element)
+                       : adjoint_t<float>(m, nrhs, u, lam, g, s, by_element);
 }
 
 }  // namespace ebe

@@ -465,8 +465,9 @@ hipError_t launch_bjacobi(const ebe_mesh* m, int level, ebe_dtype dt, int nrhs, 
                           void* y, hipStream_t s);
 
 // ---- adjoint (ebe_adjoint.hip) ---------------------------------------------
+// by_element: the kernels of meshes without fans, whichever the mesh
 hipError_t launch_adjoint(const ebe_mesh* m, ebe_dtype dt, int nrhs, const void* u,
-                          const void* lam, void* g, hipStream_t s);
+                          const void* lam, void* g, hipStream_t s, bool by_element = false);
 
 ebe_status ensure_blocks(ebe_mesh* m, hipStream_t s);
 // the geometry caches that products of (level, dtype, nrhs) read in their form
