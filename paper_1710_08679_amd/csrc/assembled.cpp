@@ -38,7 +38,7 @@ ebe_status up(DBuf& b, const std::vector<T>& h, Uploads& s) {
 
 }  // namespace
 
-ebe_status slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t>& col, const uint8_t* fix,
+bool slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t>& col, const uint8_t* fix,
                       std::vector<int32_t>& soff, std::vector<int32_t>& scol) {
   const int64_t n = int64_t(ptr.size()) - 1;
   const int64_t nsl = (n + kSliceRows - 1) / kSliceRows;
@@ -48,8 +48,7 @@ ebe_status slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t
     for (int64_t v = sl * kSliceRows; v < std::min<int64_t>(n, (sl + 1) * kSliceRows); ++v)
       width = std::max(width, ptr[v + 1] - ptr[v]);
     if (int64_t(soff[sl]) + width >= (int64_t(1) << 31) / (9 * kSliceRows)) {
-      set_error("assembled operator too large for 32-bit block indices");
-      return EBE_ERR_ARG;
+      return false;
     }
     soff[sl + 1] = soff[sl] + width;
   }
@@ -62,7 +61,7 @@ ebe_status slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t
       scol[size_t(soff[sl] + j) * kSliceRows + r] = c | (int32_t(fix[c]) << kIdxBits);
     }
   }
-  return EBE_OK;
+  return true;
 }
 
 ebe_status upload_asm(AsmOp& op, int64_t rows, const std::vector<int32_t>& soff, const std::vector<int32_t>& scol,
@@ -75,11 +74,12 @@ ebe_status upload_asm(AsmOp& op, int64_t rows, const std::vector<int32_t>& soff,
   return st;
 }
 
-ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std::vector<int32_t>& bcol,
-                        const uint8_t* fix, Uploads& s) {
+void build_level2(const std::vector<int32_t>& bptr, const std::vector<int32_t>& bcol, const uint8_t* fix,
+                  Level2Tables& t) {
   const int64_t nv = int64_t(bptr.size()) - 1;
   // aggregation (the row of v in K1 is v and its neighbours)
-  std::vector<int32_t> agg(nv, -1);
+  std::vector<int32_t>& agg = t.agg;
+  agg.assign(nv, -1);
   int32_t na = 0;
   for (int64_t v = 0; v < nv; ++v) {  // pass 1
     if (agg[v] >= 0) continue;
@@ -106,10 +106,11 @@ ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std
     ++na;
   }
   // coarse fix bits: a component is fixed when it is fixed at every member
-  std::vector<uint8_t> cfix(na, 7);
+  std::vector<uint8_t>& cfix = t.cfix;
+  cfix.assign(na, 7);
   for (int64_t v = 0; v < nv; ++v) cfix[agg[v]] &= uint8_t(fix[v] & 7);
   // P2 rows: the aggregates of v and its neighbours, increasing, padded with -1
-  int32_t width = 1;
+  int32_t& width = t.width;
   std::vector<int32_t> tmp;
   for (int64_t v = 0; v < nv; ++v) {
     tmp.clear();
@@ -117,7 +118,8 @@ ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std
     std::sort(tmp.begin(), tmp.end());
     width = std::max(width, int32_t(std::unique(tmp.begin(), tmp.end()) - tmp.begin()));
   }
-  std::vector<int32_t> pcol(size_t(nv) * width, -1);
+  std::vector<int32_t>& pcol = t.pcol;
+  pcol.assign(size_t(nv) * width, -1);
   for (int64_t v = 0; v < nv; ++v) {
     tmp.clear();
     for (int32_t k = bptr[v]; k < bptr[v + 1]; ++k) tmp.push_back(agg[bcol[k]]);
@@ -126,11 +128,12 @@ ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std
     std::copy(tmp.begin(), tmp.end(), pcol.begin() + size_t(v) * width);
   }
   if (int64_t(nv) * width >= (int64_t(1) << 31) / 9) {
-    set_error("level 2: prolongator too large for 32-bit indices");
-    return EBE_ERR_ARG;
+    t.error = "level 2: prolongator too large for 32-bit indices";
+    return;
   }
   // P2^T: for each aggregate, the P2 entries (v * width + w) naming it, in v order
-  std::vector<int32_t> toff(na + 1, 0), tidx;
+  std::vector<int32_t>&toff = t.toff, &tidx = t.tidx;
+  toff.assign(na + 1, 0);
   for (size_t i = 0; i < pcol.size(); ++i)
     if (pcol[i] >= 0) toff[pcol[i] + 1]++;
   for (int32_t a = 0; a < na; ++a) toff[a + 1] += toff[a];
@@ -141,12 +144,13 @@ ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std
       if (pcol[i] >= 0) tidx[fill[pcol[i]]++] = int32_t(i);
   }
   // A2 rows: J reached from I through P2^T, K1 and P2, increasing
-  std::vector<int32_t> aptr(na + 1, 0), acol, alen(na);
+  std::vector<int32_t> aptr(na + 1, 0), acol;
+  t.alen.resize(na);
   std::vector<int32_t> stamp(na, -1);
   for (int32_t a = 0; a < na; ++a) {
     const size_t b0 = acol.size();
-    for (int32_t t = toff[a]; t < toff[a + 1]; ++t) {
-      const int64_t v = tidx[t] / width;
+    for (int32_t i = toff[a]; i < toff[a + 1]; ++i) {
+      const int64_t v = tidx[i] / width;
       for (int32_t k = bptr[v]; k < bptr[v + 1]; ++k) {
         const int32_t* pr = pcol.data() + size_t(bcol[k]) * width;
         for (int32_t w = 0; w < width && pr[w] >= 0; ++w)
@@ -158,22 +162,27 @@ ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std
     }
     std::sort(acol.begin() + b0, acol.end());
     aptr[a + 1] = int32_t(acol.size());
-    alen[a] = aptr[a + 1] - aptr[a];
+    t.alen[a] = aptr[a + 1] - aptr[a];
   }
-  std::vector<int32_t> asoff, ascol;
-  ebe_status st = slice_rows(aptr, acol, cfix.data(), asoff, ascol);
-  if (st != EBE_OK) return st;
-  m->n_agg = na;
-  m->p2_width = width;
-  m->a2_maxlen = alen.empty() ? 0 : *std::max_element(alen.begin(), alen.end());
+  if (!slice_rows(aptr, acol, cfix.data(), t.asoff, t.ascol))
+    t.error = "assembled operator too large for 32-bit block indices";
+}
 
-  if ((st = up(m->agg, agg, s)) != EBE_OK) return st;
-  if ((st = up(m->cfix, cfix, s)) != EBE_OK) return st;
-  if ((st = up(m->p2_col, pcol, s)) != EBE_OK) return st;
-  if ((st = up(m->p2t_off, toff, s)) != EBE_OK) return st;
-  if ((st = up(m->p2t_idx, tidx, s)) != EBE_OK) return st;
-  if ((st = up(m->a2_len, alen, s)) != EBE_OK) return st;
-  return upload_asm(m->a2, na, asoff, ascol, s);
+ebe_status upload_level2(ebe_mesh* m, const Level2Tables& t, Uploads& s) {
+  if (t.error) {
+    set_error("%s", t.error);
+    return EBE_ERR_ARG;
+  }
+  m->n_agg = int64_t(t.cfix.size());
+  m->p2_width = t.width;
+  m->a2_maxlen = t.alen.empty() ? 0 : *std::max_element(t.alen.begin(), t.alen.end());
+  ebe_status st = up(m->agg, t.agg, s);
+  if (st == EBE_OK) st = up(m->cfix, t.cfix, s);
+  if (st == EBE_OK) st = up(m->p2_col, t.pcol, s);
+  if (st == EBE_OK) st = up(m->p2t_off, t.toff, s);
+  if (st == EBE_OK) st = up(m->p2t_idx, t.tidx, s);
+  if (st == EBE_OK) st = up(m->a2_len, t.alen, s);
+  return st == EBE_OK ? upload_asm(m->a2, m->n_agg, t.asoff, t.ascol, s) : st;
 }
 
 }  // namespace ebe

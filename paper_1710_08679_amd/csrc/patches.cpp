@@ -14,39 +14,15 @@
 // so its workgroups need more elements to carry the fixed cost of a patch.
 #include <algorithm>
 #include <cstring>
-#include <exception>
 #include <thread>
 #include <vector>
 
 #include "ebe_internal.h"
+#include "host_threads.h"
 
 namespace ebe {
 
 namespace {
-
-// f(0) .. f(n - 1), each on a thread of its own; the first exception is rethrown after all have ended
-template <class F>
-void parallel(int n, F f) {
-  std::vector<std::exception_ptr> err(n);
-  std::vector<std::thread> threads;
-  auto run = [&](int t) {
-    try {
-      f(t);
-    } catch (...) {
-      err[t] = std::current_exception();
-    }
-  };
-  int started = 1;  // f(0) runs here, and what no thread could be started for
-  try {
-    for (; started < n; ++started) threads.emplace_back(run, started);
-  } catch (...) {
-  }
-  run(0);
-  for (int t = started; t < n; ++t) run(t);
-  for (auto& t : threads) t.join();
-  for (auto& e : err)
-    if (e) std::rethrow_exception(e);
-}
 
 struct LevelTables {
   std::vector<int32_t> poff, pnode, pslot;      // per patch entries
