@@ -706,10 +706,16 @@ bool form_usable(const ebe_mesh* m, int order, int form, ebe_dtype dt, int nrhs)
 }
 
 namespace {
-// the mesh is one wide patch, which has no shared nodes: its products at one or
-// two cases take one launch
+// the mesh's wide patches share no nodes (it is one of them, as a rule) and its
+// patches do: products at one or two cases take one launch instead of two
 bool one_wide_patch(const ebe_mesh* m, ebe_dtype dt, int nrhs) {
-  return nrhs <= 2 && m->nfan > 0 && m->wide[wide_size(dt == EBE_F64 ? 8 : 4, nrhs)].pl.nshared == 0;
+  return nrhs <= 2 && m->nfan > 0 && m->pl[0].nshared > 0 &&
+         m->wide[wide_size(dt == EBE_F64 ? 8 : 4, nrhs)].pl.nshared == 0;
+}
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
 }
 }  // namespace
 
@@ -728,8 +734,8 @@ int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   const int f = m->form[order == 2 ? 0 : 1][dt == EBE_F64 ? 0 : 1][nrhs];
   if (form_usable(m, order, f, dt, nrhs)) return f;
   // Untuned.  The pipelined form needs a few rounds of its resident workgroups
-  // to pay for its longer patches: from here on it measured faster at nearly
-  // every number of cases, below it slower at some.  Gather / pipelined, 29x23x17
+  // to pay for its longer patches: from here on it measured faster at every number
+  // of cases (nine lattices of 144 to 32768 patches), below it slower at some.  Gather / pipelined, 29x23x17
   // lattice (1417 patches): FP64 8 cases 36.1 / 35.1 us, 11 51.9 / 48.8, 16 55.9 /
   // 52.5; FP32 5 24.2 / 25.0, 8 26.3 / 27.1, 16 34.7 / 33.6.  40x40x20 (4000): FP32 5
   // 51.3 / 52.1, 8 55.8 / 47.2, 16 89.6 / 77.3; 1 case FP64 24.8 / 25.1, FP32 18.1 /
@@ -737,8 +743,10 @@ int product_form(const ebe_mesh* m, int order, ebe_dtype dt, int nrhs) {
   // 266 / 233, 16 496 / 372.
   const int64_t from = nrhs <= kWideCases ? 6000 : (dt == EBE_F64 ? 1280 : 3000);
   // A mesh that is one wide patch has no shared nodes and so one launch instead
-  // of two: 4^3 cube, 1 case FP64 12.4 / 10.2 us, FP32 11.9 / 10.2, 2 cases 12.8 /
-  // 9.9 and 12.7 / 10.3 (3 and 4 cases: 12.8 / 16.8 and 13.1 / 14.0).
+  // of two, which is what a caller that enqueues products one by one waits for:
+  // 4^3 cube, 1 case FP64 12.4 / 10.2 us, FP32 11.9 / 10.2, 2 cases 12.8 / 9.9 and
+  // 12.7 / 10.3 (3 and 4 cases: 12.8 / 16.8 and 13.1 / 14.0).  (A mesh of a single
+  // patch of 48 elements has one launch either way: 1^3 cube 4.1 / 6.9 us.)
   if (order == 2 && (one_wide_patch(m, dt, nrhs) || m->pl[0].npatch >= from) && form_usable(m, 2, EBE_FORM_PIPELINED, dt, nrhs))
     return EBE_FORM_PIPELINED;
   return EBE_FORM_GATHER;
@@ -748,6 +756,11 @@ hipError_t launch_ebe_form(const ebe_mesh* m, int order, int form, ebe_dtype dt,
                            bool mask_in, bool bc, bool add, const int* gate, hipStream_t s, double* gamma) {
   const PatchLevel& L = m->pl[order == 2 ? 0 : 1];
   const int level = order == 2 ? 0 : 1;
+  // One launch saves a host's time, not the GPU's (4^3 cube, 1 case, FP64: 9.7 us
+  // against 7.1 of the gather form's two launches): not for a graph, then.
+  if (form == EBE_FORM_PIPELINED && order == 2 && !gamma && nrhs >= 1 && nrhs <= 2 && one_wide_patch(m, dt, nrhs) &&
+      m->fvar[0][dt == EBE_F64 ? 0 : 1][nrhs] == 0 && capturing(s))
+    form = EBE_FORM_GATHER;
   // a captured product whose form's cache could not be allocated (prepare_products)
   if ((form == EBE_FORM_PIPELINED || form == EBE_FORM_COLOURED) && nrhs >= 1 && nrhs <= EBE_MAX_RHS &&
       form_usable(m, order, form, dt, nrhs) &&

@@ -98,3 +98,30 @@ def test_tuned_variant_gives_the_same_product(middle, dtype, nrhs):
     gm.autotune(0, dt, nrhs)
     assert gm.variant(0, dt, nrhs) in (0, 1, 2)
     assert (gm.matvec(x).double() - ref).abs().max() <= 100 * np.finfo(dtype).eps * ref.abs().max()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nrhs", [1, 2])
+def test_untuned_form_of_the_smallest_meshes(gpu_lib, dtype, nrhs):
+    """Untuned, a mesh of one patch (up to 48 elements, one launch either way) takes the gather form;
+    one of several patches that make one wide patch the pipelined one, captured into a graph or not."""
+    dt = DT[dtype]
+    for grid, form in (((1, 1, 1), ebe.FORM_GATHER), ((2, 2, 2), ebe.FORM_GATHER), ((3, 3, 2), ebe.FORM_PIPELINED),
+                       ((4, 4, 4), ebe.FORM_PIPELINED)):
+        m = parity_mesh(*grid, seed=7, bc=True)
+        gm, K, kap = ebe.Mesh.from_generated(m), oracle_K(m), kappa_max(m)
+        assert gm.form(0, dt, nrhs) == form, grid
+        x = torch.zeros((m.n_nodes, 3, nrhs), dtype=dt, device="cuda")
+        y = gm.matvec(x, apply_bc=True)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            gm.matvec(x, apply_bc=True, out=y)
+        for rep in range(3):
+            xh = meshgen.rng_for(102 + rep, nrhs).standard_normal(tuple(x.shape)).astype(dtype)
+            x.copy_(torch.from_numpy(xh))
+            xr = xh.astype(np.float64)
+            ref = fem.matvec_bc(K, xr, m.fixed)
+            graph.replay()
+            for v in (y, gm.matvec(x, apply_bc=True)):
+                assert_close_bound(v.cpu().numpy().astype(np.float64), ref, abs(K), xr, dtype, kap, f"{grid} {rep}")
