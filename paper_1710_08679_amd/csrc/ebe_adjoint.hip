@@ -14,7 +14,7 @@
 // its loads (bytes at 64x64x32 hexahedra x 6, FP64, 4 cases: 0.26 GB); one
 // work-item per (element, case) with the elements dealt to the XCDs in turn
 // took 240 us there.  The element-by-element kernels below serve meshes
-// without fans (2^25 nodes or more).
+// without fans (2^25 nodes or more) and small ones.
 #include <hip/hip_runtime.h>
 
 #include "patch_common.h"
@@ -261,7 +261,13 @@ hipError_t adjoint_t(const ebe_mesh* m, int nrhs, const void* u, const void* lam
 
 hipError_t launch_adjoint(const ebe_mesh* m, ebe_dtype dt, int nrhs, const void* u, const void* lam,
                           void* g, hipStream_t s, bool by_element) {
-  by_element |= m->nfan == 0;
+  // A fan is three tetrahedra long: where every (element, case) can be resident at
+  // once and a wavefront holds an element's cases, those end sooner (by fans / by
+  // elements: 4^3 cube FP64 1 case 7.0 / 5.3 us, 18x18x12 lattice, 23328 elements,
+  // 1 case 8.8 / 6.0, 4 cases 8.4 / 8.6, 8 cases 8.7 / 10.9; FP32 4 cases 7.2 / 6.5, 8
+  // 6.9 / 8.2; 67,000 elements 1 case 9.0 / 8.9, FP32 7.4 / 7.6).
+  const int64_t resident = dt == EBE_F64 ? 80000 : 96000;
+  by_element |= m->nfan == 0 || ((nrhs & (nrhs - 1)) == 0 && m->n_elem * nrhs < resident);
   return dt == EBE_F64 ? adjoint_t<double>(m, nrhs, u, lam, g, s, by_element)
                        : adjoint_t<float>(m, nrhs, u, lam, g, s, by_element);
 }

@@ -465,7 +465,7 @@ hipError_t launch_bjacobi(const ebe_mesh* m, int level, ebe_dtype dt, int nrhs, 
                           void* y, hipStream_t s);
 
 // ---- adjoint (ebe_adjoint.hip) ---------------------------------------------
-// by_element: the kernels of meshes without fans, whichever the mesh
+// by_element: the kernels of small meshes and of those without fans, whichever the mesh
 hipError_t launch_adjoint(const ebe_mesh* m, ebe_dtype dt, int nrhs, const void* u,
                           const void* lam, void* g, hipStream_t s, bool by_element = false);
 

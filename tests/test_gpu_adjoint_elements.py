@@ -1,6 +1,7 @@
 """The adjoint element gradient by single elements, which meshes of 2^25 nodes or
-more take (too large for a test): called here on small ones through the
-library's own launcher, against the oracle and the kernel by fans."""
+more take (too large for a test), small ones at some numbers of cases: called
+here through the library's own launcher, against the oracle; and the entry
+point on either side of the size from which it goes by fans."""
 import ctypes
 
 import numpy as np
@@ -64,3 +65,20 @@ def test_sixteen_cases_by_elements_are_spread_over_lanes(gpu_lib, dtype):
             runs.append(a.elapsed_time(b))
         times[n] = min(runs)
     assert times[16] < times[15], times
+
+
+@pytest.mark.parametrize("dtype, tol", [(np.float64, 1e-12), (np.float32, 2e-5)])
+@pytest.mark.parametrize("nrhs, grid", [(1, (23, 24, 24)), (1, (24, 24, 24)), (1, (25, 26, 25)), (4, (14, 15, 15)),
+                                        (4, (15, 15, 15)), (4, (16, 16, 16)), (16, (8, 9, 11)), (16, (9, 10, 10)),
+                                        (16, (10, 10, 11))])
+def test_gradient_around_the_size_of_a_resident_mesh(gpu_lib, dtype, tol, nrhs, grid):
+    """80000 (FP64) or 96000 elements times cases: below and above, by the entry point and by elements."""
+    m = meshgen.crust_mesh(*grid)
+    gm = ebe.Mesh.from_generated(m)
+    rng = meshgen.rng_for(103, nrhs)
+    u, lam = (rng.standard_normal((m.n_nodes, 3, nrhs)).astype(dtype) for _ in range(2))
+    free = 1.0 - m.fixed[:, :, None].astype(np.float64)
+    ref = adjoint.element_gradient(m.xyz, m.conn, m.poisson, u * free, lam * free)
+    ud, ld = torch.from_numpy(u).cuda(), torch.from_numpy(lam).cuda()
+    for g in (by_elements(gm, ud, ld), gm.adjoint_grad(ud, ld)):
+        assert np.max(np.abs(g.cpu().numpy() - ref)) <= tol * np.max(np.abs(ref))
