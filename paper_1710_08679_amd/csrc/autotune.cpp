@@ -53,7 +53,8 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
     // assembled form comes in three tiles, and the pipelined form of the
     // quadratic level goes by the default of its size, by single elements or by
     // fans: measure them all (coloured, which comes behind the pipelined form,
-    // only its default)
+    // only its default).  The pipelined default, which chooses anew for products
+    // with (x, K x), gives way to a variant that is faster by 3% only.
     const bool curved = order == 2 && m->curved;
     const int nvar = form == EBE_FORM_ASSEMBLED || (form == EBE_FORM_PIPELINED && level == 0)
                          ? 3
@@ -62,6 +63,7 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
                         (form == EBE_FORM_DETERMINISTIC && m->pl[0].coff.size() > 1))
                          ? 2
                          : 1;
+    const double margin = level == 0 && form == EBE_FORM_PIPELINED ? 0.97 : 1.0;
     for (int var = 0; var < nvar && e == hipSuccess; ++var) {
       m->fvar[lv][k][nrhs] = 0;
       const QuadKernel usual = quad_kernel(m, form, dt, nrhs, false);
@@ -75,7 +77,7 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
         if (e == hipSuccess) e = hipEventSynchronize(b);
         float t = 0.f;
         if (e == hipSuccess) e = hipEventElapsedTime(&t, a, b);
-        if (e == hipSuccess && double(t) < best[form]) {
+        if (e == hipSuccess && double(t) < best[form] * (var != best_var[form] ? margin : 1.0)) {
           best[form] = double(t);
           best_var[form] = var;
         }
