@@ -677,10 +677,7 @@ ebe_status ensure_stage(ebe_mesh* m, int nrhs, size_t elem_bytes) {
       set_error("mesh too large for 32-bit staging indices (%lld slots)", (long long)L.nslots);
       return EBE_ERR_ARG;
     }
-    int64_t slots = L.nslots;
-    if (l == 0 && nrhs <= kWideCases)
-      slots = std::max(slots, m->wide[wide_size(int(elem_bytes), nrhs)].pl.nslots);
-    const size_t need = size_t(slots) * 3 * size_t(nrhs) * elem_bytes;
+    const size_t need = size_t(L.nslots) * 3 * size_t(nrhs) * elem_bytes;
     ebe_status st = m->pl[l].stage.alloc(need);
     if (st != EBE_OK) return st;
   }

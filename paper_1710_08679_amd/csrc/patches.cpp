@@ -662,6 +662,13 @@ ebe_status build_patches(ebe_mesh* m, const int32_t* conn10, const uint8_t* fix,
   if (fans) {
     ChainTables c;
     build_chains(t[0], m->n_nodes, fix, pfan, cword, fanw, c);
+    // (the chains and wide patches stage in pl[0].stage: a run of patches shares
+    // no more rows with others than its parts do)
+    if (std::max({c.t.nslots, w[0].t.nslots, w[1].t.nslots}) > t[0].nslots) {
+      set_error("build_patches: %lld staged rows of chains or wide patches exceed %lld",
+                (long long)std::max({c.t.nslots, w[0].t.nslots, w[1].t.nslots}), (long long)t[0].nslots);
+      return EBE_ERR_INDEX;
+    }
     m->nfan = int64_t(felem.size()) / kFanLen;
     if ((st = up(m->pfan, pfan, s)) != EBE_OK) return st;
     if ((st = up(m->fanw, fanw, s)) != EBE_OK) return st;

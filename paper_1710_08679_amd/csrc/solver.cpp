@@ -25,8 +25,6 @@ using namespace ebe;
 
 namespace {
 
-constexpr int kMaxBlocks = 256;  // workgroups that leave partial sums (solver_kernels.hip)
-
 struct Bufs {
   double *r, *p, *q;  // outer, [N][3][n] FP64
   void *rb, *ub, *e0, *p0, *q0;  // level 0

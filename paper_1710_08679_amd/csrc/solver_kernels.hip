@@ -28,7 +28,6 @@ namespace {
 // p = z + beta p averaged over the levels: 10.4 -> 8.9 us).  Systems too small
 // for that use smaller workgroups, so they still spread over the CUs.
 constexpr int kMaxThreads = 1024;
-constexpr int kMaxBlocks = 256;
 constexpr int kMaxBlocksNoSum = 512;
 
 __host__ __device__ constexpr int block_for(int threads, int nr) { return (threads / nr) * nr; }

@@ -9,6 +9,9 @@
 
 namespace ebe {
 
+// workgroups of a vector kernel that leave partial sums: rows of SolverState::partials
+constexpr int kMaxBlocks = 256;
+
 struct InnerScalars {          // Algorithm 1(b), one set per level
   double nr2[EBE_MAX_RHS];     // ||r_j||^2 of the inner right-hand side
   double rho_a[EBE_MAX_RHS];    // (M^-1 e, e) of the current step
