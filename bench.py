@@ -590,7 +590,7 @@ def main():
             "frac_of_plain_fma_peak": F / t / 1e12 / PLAIN_FMA_PEAK_TFLOPS,
             "ops_model": f"E*({OPS_PER_ELEM_RHS}n+{OPS_PER_ELEM}) VALU ops per product, FMA = 2 flops",
             "kernel": f"EBE product FP32 n=16, {form} form (ebe_matvec: "
-                      + ("one k_ebe_pipe launch per patch colour" if form == "coloured" else
+                      + ("one patch kernel launch per colour" if form == "coloured" else
                          "patch kernel + shared-node pass") + ")",
             "launches_per_product": gm.patch_info(0)["colours"] if form == "coloured" else 2,
             "ms_per_product": ms_events,

@@ -77,10 +77,11 @@ typedef int32_t ebe_dtype;
  * speed): GATHER reads each element's nodal values straight from x; STAGED
  * copies a patch's node rows into LDS first, a few cases at a time;
  * PIPELINED is GATHER in persistent workgroups that fetch the next patch's
- * metadata while computing the current one (on the quadratic level with the
- * patch's tetrahedra taken in fans around common edges, so nodes that
- * neighbouring tetrahedra share are read and added once, and at up to four
- * cases on wider patches, one workgroup each); ASSEMBLED (linear level only)
+ * metadata while computing the current one (on the quadratic level, from some
+ * size on that depends on dtype and nrhs, with the patch's tetrahedra taken in
+ * fans around common edges, so nodes that neighbouring tetrahedra share are
+ * read and added once, and at up to four cases on wider patches, one workgroup
+ * each); ASSEMBLED (linear level only)
  * applies K1 assembled once (per material) into 3x3 blocks over the corner
  * graph instead of forming element products, so a product reads each block
  * once for all cases: a departure from the paper's element-by-element
@@ -102,9 +103,13 @@ typedef int32_t ebe_dtype;
  * most 8 (FP32) or 4 (FP64).
  * PIPELINED and COLOURED need a mesh below 2^25 nodes whose vectors at this
  * (dtype, nrhs) are below 4 GiB; elsewhere GATHER runs in their place.
- * AUTO: the mesh's tuned choice, else a default: GATHER, or PIPELINED on
- * quadratic meshes of several thousand patches (48 elements each), or of up
- * to 384 elements at one or two cases. */
+ * AUTO: the mesh's tuned choice, else a default: GATHER, or on the quadratic
+ * level PIPELINED from 6000 patches (of at most 48 elements) at up to four
+ * cases, from 1280 (FP64) or 3000 (FP32) at more, and at one or two cases
+ * where the mesh's patches put together in runs of up to 384 elements share no
+ * nodes (a 4^3 cube; into a graph the gather form is captured there).  A
+ * PIPELINED or COLOURED product that is captured before the element geometry
+ * it reads was allocated runs as GATHER. */
 typedef enum {
   EBE_FORM_AUTO = -1,
   EBE_FORM_GATHER = 0,
@@ -222,7 +227,8 @@ void ebe_mesh_destroy(ebe_mesh* mesh);
  * (corners): element patches (consecutive elements whose nodal sums fit a
  * workgroup's LDS), nodes shared by several patches, staged partial-sum rows
  * (one per (patch, shared node) pair: what the staging forms write and the
- * node-centric pass reads back), and colours of the COLOURED form (0 at
+ * node-centric pass reads back; PIPELINED by fans on level 0 stages fewer, its
+ * patches handing rows on or being put together), and colours of the COLOURED form (0 at
  * level 1).  Any out pointer may be NULL. */
 ebe_status ebe_patch_info(const ebe_mesh* mesh, int32_t level, int64_t* n_patches, int64_t* n_shared,
                           int64_t* n_staged, int32_t* n_colours);

@@ -227,7 +227,7 @@ k_ebe_wide(const uint16_t* __restrict__ fanl, const int32_t* __restrict__ felem,
           put(lid(a), c, fd[a][c]);
         }
     }
-    w += TPB;  // (a full patch of full fans takes one trip)
+    w += TPB;  // (a full patch of full fans takes one trip, two in FP64 at 3 and 4 cases)
     fetch();
   }
   if constexpr (GAMMA && kLaneCase) {
