@@ -53,7 +53,8 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
     // assembled form comes in three tiles, and the pipelined form of the
     // quadratic level goes by the default of its size, by single elements or by
     // fans: measure them all (coloured, which comes behind the pipelined form,
-    // only its default).  The pipelined default, which chooses anew for products
+    // only its default; pipelined, the others only within a factor two of the
+    // size where the default changes).  The pipelined default, which chooses anew for products
     // with (x, K x), gives way to a variant that is faster by 3% only.
     const bool curved = order == 2 && m->curved;
     const int nvar = form == EBE_FORM_ASSEMBLED || (form == EBE_FORM_PIPELINED && level == 0)
@@ -68,7 +69,10 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
       m->fvar[lv][k][nrhs] = 0;
       const QuadKernel usual = quad_kernel(m, form, dt, nrhs, false);
       m->fvar[lv][k][nrhs] = int8_t(var);
-      if (level == 0 && form == EBE_FORM_PIPELINED && var > 0 && quad_kernel(m, form, dt, nrhs, false) == usual) continue;
+      if (level == 0 && form == EBE_FORM_PIPELINED && var > 0) {
+        const int64_t from = kFanFrom[0][k][nrhs], n = m->pl[0].npatch;
+        if (quad_kernel(m, form, dt, nrhs, false) == usual || 2 * n < from || n > 2 * from) continue;
+      }
       e = launch_ebe_form(m, order, form, dt, nrhs, x, y, false, m->has_bc, false, nullptr, s);  // warm-up
       for (int r = 0; r < kRuns && e == hipSuccess; ++r) {
         e = hipEventRecord(a, s);
