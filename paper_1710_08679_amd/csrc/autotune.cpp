@@ -54,8 +54,9 @@ ebe_status tune_product(ebe_mesh* m, int level, ebe_dtype dt, int nrhs, const vo
     // quadratic level goes by the default of its size, by single elements or by
     // fans: measure them all (coloured, which comes behind the pipelined form,
     // only its default; pipelined, the others only within a factor two of the
-    // size where the default changes).  The pipelined default, which chooses anew for products
-    // with (x, K x), gives way to a variant that is faster by 3% only.
+    // size where the default changes).  The pipelined default, which chooses
+    // anew for products with (x, K x), gives way to a variant that is faster by
+    // 3% only.
     const bool curved = order == 2 && m->curved;
     const int nvar = form == EBE_FORM_ASSEMBLED || (form == EBE_FORM_PIPELINED && level == 0)
                          ? 3
