@@ -63,11 +63,12 @@ void DBuf::release() {
   owned_ = false;
 }
 
+// (a null host: memory for a table that the GPU forms)
 ebe_status Uploads::add(DBuf& b, const void* host, size_t bytes) {
   if (bytes > kSmall) {
     ebe_status st = b.alloc(bytes);
     if (st != EBE_OK) return st;
-    EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), host, bytes, hipMemcpyHostToDevice, s_));
+    if (host) EBE_TRY_HIP(hipMemcpyAsync(b.as<void>(), host, bytes, hipMemcpyHostToDevice, s_));
     return EBE_OK;
   }
   const size_t at = (host_.size() + 255) / 256 * 256;
@@ -388,9 +389,9 @@ static ebe_status create_mesh(const char* fn, bool curved, const double* xyz, in
     }
   }
   if (st == EBE_OK) st = upload_level2(m, level2, up);
+  if (st == EBE_OK && m->nfan > 0) st = up.add(m->pl[0].ptab, nullptr, size_t(E) * 10 * sizeof(uint32_t));
   if (st == EBE_OK) st = up.finish(m->small_tables);
   if (st == EBE_OK) st = m->gacc.alloc(kGammaBytes);
-  if (st == EBE_OK && m->nfan > 0) st = m->pl[0].ptab.alloc(size_t(E) * 10 * sizeof(uint32_t));
   if (st == EBE_OK) {
     hipError_t he = launch_lame(m, s);
     if (he == hipSuccess) he = launch_fill_zero(m->gacc.as<void>(), kGammaBytes, s);
